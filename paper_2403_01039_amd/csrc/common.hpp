@@ -158,6 +158,15 @@ __device__ inline float closure_dg(float dref, float delta, int kind, int order)
   return closure_g(dnew, kind, order) - closure_g(dref, kind, order);
 }
 
+// 1 / sqrt(a) in FP64 (a normal, positive): the hardware estimate (relative error
+// e0 ~ 2^-24) and one step of third order, y (1 + e/2 + 3 e^2 / 8) with
+// e = 1 - a y^2, whose own error is of order e0^3, below FP64 round-off.
+__device__ __forceinline__ double rsqrt_nr(double a) {
+  const double y = __builtin_amdgcn_rsq(a);
+  const double e = fma(-a * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
 // Batched launches: blockIdx.y selects the member of a batch whose
 // workspaces lie bstride bytes apart (bstride = 0 and one member for a single
 // solve).  Null pointers stay null.

@@ -8,7 +8,13 @@
 namespace rism {
 
 constexpr int kPotThreads = 256;
-constexpr int kPotChunk = 256;   // atoms staged in LDS per round
+
+// K consecutive floats in one store (K = 2 or 4, p aligned to it).
+template <int K>
+__device__ __forceinline__ void store_k(float* __restrict__ p, const float* v) {
+  if constexpr (K == 4) *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+  else *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
+}
 
 // Solute atoms relative to the grid corner r0 (with the charge in .w), and per
 // (atom, site) LJ coefficients beta*4*eps*sigma^12 and beta*4*eps*sigma^6
@@ -29,71 +35,141 @@ __global__ void k_prep_atoms(const double* __restrict__ xyz, const double* __res
   }
 }
 
+// e^{-d} in FP64 for d >= 0, to about 1 ulp: d = -(n ln 2 + r) with |r| <= ln(2)/2,
+// the Taylor polynomial of e^r of degree 12 (remainder r^13 / 13! < 2e-16),
+// scaled by 2^n.  ln 2 is its double plus the remainder.  The coefficients sit
+// in scalar registers (the empty asm hides their values): as literals each
+// would be moved into vector registers again for every term.
+struct ExpNeg {
+  double c[13] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040,
+                  1.0 / 40320, 1.0 / 362880, 1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600};
+  double l2e = -1.4426950408889634, hi = -0.69314718055994529, lo = -2.3190468138462996e-17;
+  __device__ __forceinline__ ExpNeg() {
+#pragma unroll
+    for (int i = 2; i < 13; ++i) asm("" : "+s"(c[i]));
+    asm("" : "+s"(l2e));
+    asm("" : "+s"(hi));
+    asm("" : "+s"(lo));
+  }
+  // K values at a time, term by term: K independent chains
+  template <int K>
+  __device__ __forceinline__ void run(const double (&d)[K], double (&out)[K]) const {
+    double n[K], r[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      n[k] = rint(d[k] * l2e);
+      r[k] = fma(n[k], lo, fma(n[k], hi, -d[k]));
+      out[k] = fma(r[k], c[12], c[11]);
+    }
+#pragma unroll
+    for (int i = 10; i >= 0; --i)
+#pragma unroll
+      for (int k = 0; k < K; ++k) out[k] = fma(out[k], r[k], c[i]);
+#pragma unroll
+    for (int k = 0; k < K; ++k) out[k] = ldexp(out[k], (int)n[k]);
+  }
+};
+
 // w_g = min(beta u_g, cap) - f_g and phi_lr on every grid point.
 //   beta u_g = sum_a [beta LJ_ag(dc) + coul_g q_a / dc],  dc = max(d, D_MIN)
 //   f_g      = coul_g * phi_lr,  phi_lr = sum_a q_a (1 - e^{-d}) / d
-// The uncapped w is accumulated directly as beta LJ + coul_g * phi_sr with
+// Two FP64 sums hold the Coulomb part: phi = sum_a q_a / dc and the short-ranged
 //   phi_sr = sum_a q_a s(d),  s(d) = e^{-d}/d (d >= D_MIN),
 //                             s(d) = 1/D_MIN - (1 - e^{-d})/d (d < D_MIN),
-// which equals q/dc - q (1 - e^{-d})/d term by term and avoids subtracting two
-// long-ranged sums.  Pair terms and sums are FP64 (the twelfth power of a
+// so that phi_lr = phi - phi_sr, and the uncapped w is accumulated directly as
+// beta LJ + coul_g phi_sr.  Pair terms and sums are FP64 (the twelfth power of a
 // rounded FP32 distance would cost ~1e-5 relative in w near the solute).
-template <int NV>
+//
+// Bound by the FP64 issue rate.  A thread takes K points that follow each other
+// in x: they share the atom's data, read at a wave-uniform address (scalar
+// loads), and dy^2 + dz^2; and their K independent chains hide the FP64
+// latency.  1/dc and dc come from one reciprocal square root, e^{-d} from
+// ExpNeg, skipped where no point of the wave is within 38 A (there it adds
+// below FP64 resolution).  128^3, 200 atoms, 5 sites: 1439 us with a square root,
+// two divisions and the library's exp at one point a thread, 611 us now (45 FP64
+// operations a pair, 0.79 of the FP64 issue rate).
+template <int NV, int K>
 __global__ __launch_bounds__(kPotThreads) void k_potential(
     const double4* __restrict__ atoms, const double2* __restrict__ lj, int n_atoms, int nx, int ny,
     int nz, double dr, SiteConsts sc, float* __restrict__ w, float* __restrict__ phi_out) {
-  __shared__ double4 s_at[kPotChunk];
-  __shared__ double2 s_lj[kPotChunk * NV];
-  const size_t N = (size_t)nx * ny * nz;
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool live = idx < N;
-  const int ix = (int)(idx % nx);
-  const int iy = (int)((idx / nx) % ny);
-  const int iz = (int)(idx / ((size_t)nx * ny));
-  const double px = ix * dr, py = iy * dr, pz = iz * dr;
-  double acc[NV];
+  const size_t N = (size_t)nx * ny * nz;   // a multiple of K, as nx is
+  const unsigned idx = (blockIdx.x * kPotThreads + threadIdx.x) * K;   // N <= 512^3
+  if (idx >= N) return;
+  const unsigned row = idx / (unsigned)nx;
+  const int ix = (int)(idx - row * nx), iz = (int)(row / (unsigned)ny), iy = (int)(row - iz * ny);
+  const double py = iy * dr, pz = iz * dr;
+  double px[K], acc[K][NV], phi[K], phi_sr[K];
 #pragma unroll
-  for (int g = 0; g < NV; ++g) acc[g] = 0.0;
-  double phi_sr = 0.0, phi_lr = 0.0;
-  for (int a0 = 0; a0 < n_atoms; a0 += kPotChunk) {
-    const int cnt = (n_atoms - a0) < kPotChunk ? (n_atoms - a0) : kPotChunk;
-    __syncthreads();
-    for (int t = threadIdx.x; t < cnt; t += blockDim.x) s_at[t] = atoms[a0 + t];
-    for (int t = threadIdx.x; t < cnt * NV; t += blockDim.x) s_lj[t] = lj[(size_t)a0 * NV + t];
-    __syncthreads();
-    if (live) {
-      for (int a = 0; a < cnt; ++a) {
-        const double4 at = s_at[a];
-        const double dx = px - at.x, dy = py - at.y, dz = pz - at.z;
-        const double d = sqrt(dx * dx + dy * dy + dz * dz);
-        const double dc = fmax(d, kDMin);
-        const double inv = 1.0 / dc;
-        // beyond 38 A, e^{-d} < 2^-54: 1 - e^{-d} rounds to 1 and e^{-d}/d adds
-        // below FP64 resolution, so the exponential is skipped there
-        const double e = d < 38.0 ? exp(-d) : 0.0;
-        // (1 - e^{-d})/d with screening length 1 A; expm1 only where 1 - e^{-d} cancels
-        const double lr = (d < 0.5) ? ((d > 1.0e-300) ? -expm1(-d) / d : 1.0) : (1.0 - e) / d;
-        const double sr = (d >= kDMin) ? e * inv : 1.0 / kDMin - lr;
-        phi_lr += at.w * lr;
-        phi_sr += at.w * sr;
-        const double s2 = inv * inv;
-        const double s6 = s2 * s2 * s2;
+  for (int k = 0; k < K; ++k) {
+    px[k] = (ix + k) * dr;
+    phi[k] = phi_sr[k] = 0.0;
 #pragma unroll
-        for (int g = 0; g < NV; ++g) {
-          const double2 c = s_lj[a * NV + g];
-          acc[g] += (c.x * s6 - c.y) * s6;
-        }
+    for (int g = 0; g < NV; ++g) acc[k][g] = 0.0;
+  }
+  const ExpNeg ex;
+  for (int a = 0; a < n_atoms; ++a) {
+    const double4 at = atoms[a];
+    const double2* la = lj + (size_t)a * NV;
+    const double dy = py - at.y, dz = pz - at.z;
+    const double dyz = dy * dy + dz * dz;
+    double d2[K], inv[K], q[K];
+    double least = 1.0e300;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const double dx = px[k] - at.x;
+      d2[k] = dx * dx + dyz;
+      least = fmin(least, d2[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      inv[k] = rsqrt_nr(fmax(d2[k], kDMin * kDMin));
+      q[k] = at.w * inv[k];
+      phi[k] += q[k];
+    }
+    if (least < 38.0 * 38.0) {
+      double d[K], e[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) d[k] = fmax(d2[k], kDMin * kDMin) * inv[k];
+      ex.run<K>(d, e);
+      if (least < kDMin * kDMin) {   // a point on an atom: s(d) in its clamped form
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+          if (d2[k] < kDMin * kDMin) {
+            const double t = sqrt(d2[k]);
+            e[k] = 1.0 - kDMin * ((t > 1.0e-300) ? -expm1(-t) / t : 1.0);
+          }
+      }
+#pragma unroll
+      for (int k = 0; k < K; ++k) phi_sr[k] += q[k] * e[k];
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const double s2 = inv[k] * inv[k];
+      const double s6 = s2 * s2 * s2;
+#pragma unroll
+      for (int g = 0; g < NV; ++g) {
+        const double2 c = la[g];
+        acc[k][g] += (c.x * s6 - c.y) * s6;
       }
     }
   }
-  if (!live) return;
+#pragma unroll
+  for (int k = 0; k < K; ++k) phi[k] -= phi_sr[k];   // phi_lr
 #pragma unroll
   for (int g = 0; g < NV; ++g) {
     const double coul = sc.coul64[g];
-    const double bu = acc[g] + coul * (phi_sr + phi_lr);
-    w[(size_t)g * N + idx] = (float)((bu > kBetaUCap) ? kBetaUCap - coul * phi_lr : acc[g] + coul * phi_sr);
+    float o[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const double u = acc[k][g] + coul * phi_sr[k];
+      o[k] = (float)((u + coul * phi[k] > kBetaUCap) ? kBetaUCap - coul * phi[k] : u);
+    }
+    store_k<K>(w + (size_t)g * N + idx, o);
   }
-  phi_out[idx] = (float)phi_lr;
+  float o[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) o[k] = (float)phi[k];
+  store_k<K>(phi_out + idx, o);
 }
 
 __device__ inline double kappa_of(int j, int n, double dk) {
@@ -131,30 +207,77 @@ __global__ void k_phase_tables(const double* __restrict__ xyz, int n_atoms, int 
 // divided by dV (the forward FFT is unnormalised):
 //   F(k) = (4 pi beta C / l^2) / (|k|^2 (|k|^2 + l^-2)) / dV * sum_a q_a e^{-i k.(R_a - r0)}
 // so that f~_g / dV = q_g F (the 1/N of the inverse sits in the Q table).  The
-// other half follows from F(-k) = conj F(k).
-__global__ void k_ftilde(const double2* __restrict__ ph, const double4* __restrict__ atoms,
-                         int n_atoms, int nx, int ny, int nz, double dkx, double dky, double dkz,
-                         double pref, double2* __restrict__ F) {
-  const size_t N = (size_t)nx * ny * nz;
-  const size_t half = (N + 1) / 2;
-  const size_t L = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (L >= half) return;
-  const int jx = (int)(L % nx);
-  const int jy = (int)((L / nx) % ny);
-  const int jz = (int)(L / ((size_t)nx * ny));
+// other half follows from F(-k) = conj F(k).  nz is even, so the first half is
+// the planes jz < nz / 2.
+//
+// The sum is a complex matrix product over the atoms, (row (jz, jy)) x (column
+// jx): the row factor q_a e^{..z} e^{..y} is formed once per workgroup and atom
+// instead of once per k-point.  A workgroup owns kFtRows rows x kFtCols columns,
+// staging kFtAtoms atoms at a time in LDS; a thread holds 4 rows (wave-uniform,
+// LDS broadcasts) x 2 columns, 32 FP64 FMAs per 6 LDS reads, and is bound by
+// the two together.  128^3, 200 atoms: 325 us with one k-point a thread, which
+// formed both products anew for each, 79 us now.
+constexpr int kFtRows = 16, kFtCols = 128, kFtAtoms = 16;
+
+__global__ __launch_bounds__(256) void k_ftilde(const double2* __restrict__ ph,
+                                                const double4* __restrict__ atoms, int n_atoms,
+                                                int nx, int ny, int nz, double dkx, double dky,
+                                                double dkz, double pref,
+                                                double2* __restrict__ F) {
+  __shared__ double2 ex[kFtAtoms][kFtCols];
+  __shared__ double2 left[kFtAtoms][kFtRows];
   const int nsum = nx + ny + nz;
-  double sx = 0.0, sy = 0.0;
-  for (int a = 0; a < n_atoms; ++a) {
-    const double2* pa = ph + (size_t)a * nsum;
-    const double2 e = cmul(cmul(pa[jx], pa[nx + jy]), pa[nx + ny + jz]);
-    const double qa = atoms[a].w;
-    sx += qa * e.x;
-    sy += qa * e.y;
+  const int rows = (nz / 2) * ny;
+  const int r0 = blockIdx.x * kFtRows, c0 = blockIdx.y * kFtCols;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double2 s[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s[i][0] = s[i][1] = make_double2(0.0, 0.0);
+  for (int a0 = 0; a0 < n_atoms; a0 += kFtAtoms) {
+    __syncthreads();   // the previous atoms' factors are read
+    for (int t = threadIdx.x; t < kFtAtoms * kFtCols; t += 256) {
+      const int a = a0 + t / kFtCols, j = c0 + t % kFtCols;
+      ex[t / kFtCols][t % kFtCols] =
+          a < n_atoms && j < nx ? ph[(size_t)a * nsum + j] : make_double2(0.0, 0.0);
+    }
+    for (int t = threadIdx.x; t < kFtAtoms * kFtRows; t += 256) {
+      const int a = a0 + t / kFtRows, r = r0 + t % kFtRows;
+      double2 v = make_double2(0.0, 0.0);
+      if (a < n_atoms && r < rows) {
+        const double2* pa = ph + (size_t)a * nsum;
+        v = cscale(cmul(pa[nx + r % ny], pa[nx + ny + r / ny]), atoms[a].w);
+      }
+      left[t / kFtRows][t % kFtRows] = v;
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int a = 0; a < kFtAtoms; ++a) {
+      const double2 e0 = ex[a][lane], e1 = ex[a][lane + 64];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double2 l = left[a][wave * 4 + i];
+        s[i][0].x = fma(l.x, e0.x, fma(-l.y, e0.y, s[i][0].x));
+        s[i][0].y = fma(l.x, e0.y, fma(l.y, e0.x, s[i][0].y));
+        s[i][1].x = fma(l.x, e1.x, fma(-l.y, e1.y, s[i][1].x));
+        s[i][1].y = fma(l.x, e1.y, fma(l.y, e1.x, s[i][1].y));
+      }
+    }
   }
-  const double kx = kappa_of(jx, nx, dkx), ky = kappa_of(jy, ny, dky), kz = kappa_of(jz, nz, dkz);
-  const double k2 = kx * kx + ky * ky + kz * kz;
-  const double s = pref / (k2 * (k2 + 1.0 / (kScreen * kScreen)));
-  F[L] = make_double2(s * sx, s * sy);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = r0 + wave * 4 + i;
+    if (r >= rows) break;
+    const double ky = kappa_of(r % ny, ny, dky), kz = kappa_of(r / ny, nz, dkz);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int jx = c0 + lane + 64 * h;
+      if (jx >= nx) continue;
+      const double kx = kappa_of(jx, nx, dkx);
+      const double k2 = kx * kx + ky * ky + kz * kz;
+      const double f = pref / (k2 * (k2 + 1.0 / (kScreen * kScreen)));
+      F[(size_t)r * nx + jx] = make_double2(f * s[i][h].x, f * s[i][h].y);
+    }
+  }
 }
 
 // Interpolation tables with the 1/N of the inverse transform folded in:

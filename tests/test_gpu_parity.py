@@ -88,6 +88,26 @@ def test_potential_matches_oracle(R, O, name):
         assert np.abs(phi - phi_ref).max() / max(1.0, np.abs(phi_ref).max()) < 2e-5
 
 
+@pytest.mark.parametrize("shape", [(64, 128, 128), (96, 128, 90), (30, 20, 18)])
+def test_potential_points_per_thread(R, O, shape):
+    """Four points a thread (2^20 points or more, rows of a multiple of four) and
+    two (other rows, smaller grids), with one atom on a grid point and points
+    beyond 38 A of every atom.  Pair terms and sums are FP64 on both sides, so w
+    and phi_lr differ by the float32 rounding of the result: 2^-24 relative, here
+    1.5e-7 of max(1, |value|) with both sides' summation order."""
+    prob = inputs.small_problem(4, n_atoms=4, shape=shape, saline=True, radius=2.0)
+    prob.solute.xyz[0] = np.array(prob.grid.center) + np.array([-1.0, 0.5, 1.5])
+    print(f"potential {shape}", flush=True)
+    s, chi, dk = _run(R, prob)
+    w, phi = (t.cpu().numpy() for t in s.fields())
+    sys_ = O.build_system(prob, chi, dk)
+    w_ref = sys_.beta_u - sys_.f
+    q_v = prob.solvent.site_arrays()[0]
+    phi_ref = sys_.f[0] / (sys_.beta * O.COULOMB * q_v[0])
+    assert (np.abs(w - w_ref) / np.maximum(1.0, np.abs(w_ref))).max() < 1.5e-7
+    assert (np.abs(phi - phi_ref) / np.maximum(1.0, np.abs(phi_ref))).max() < 1.5e-7
+
+
 # (saline, (nz, ny, nx)): the generic path, the fused x kernels with the fused
 # z transform + contraction, and every fused instantiation the workloads reach
 # at full size: x and z lengths 96 (96^3 batch members), x 256 and z 256 (the
