@@ -15,13 +15,20 @@
 // nothing.  Pair terms and sums are FP64; g is the float32 field the solve
 // returns.
 //
-// Work split: a workgroup holds 64 atoms (one per lane; its four waves take the
-// same atoms) and walks tiles of 256 grid points.  A tile's per-point data
+// Work split: a workgroup holds 64 A atoms (A per lane, 64 apart; its four waves
+// take the same atoms) and walks tiles of 256 grid points.  A tile's per-point data
 // (coordinates, rho_g g_g, and the atom-independent Coulomb weight
 // sum_g rho_g g_g coul_g) sit in LDS and are read as broadcasts; points where
 // every g_g is 0 (inside the solute core) are skipped by whole waves.  Each
 // workgroup leaves one FP64 partial per (atom, component); a second kernel adds
 // them in a fixed order, so the result does not depend on scheduling.
+//
+// With one atom a lane the n_v + 5 LDS reads of a point cost the compute unit
+// more cycles than the pair's FP64 arithmetic; with two the arithmetic bounds
+// (200 atoms, 128^3, 5 sites: 765 us at A = 1, 690 at 2, 675 at 4, which wastes
+// more lanes at other atom counts; 1230 us before, with a square root and a
+// division for 1/d and one atom a lane).  At most 32 atoms leave lanes over: the
+// wave then takes 2 or 4 points at a time, each for `lanes` = 32 or 16 lanes.
 #pragma once
 
 #include "common.hpp"
@@ -29,34 +36,40 @@
 namespace rism {
 
 constexpr int kGradThreads = 256;       // four waves
-constexpr int kGradAtoms = 64;          // atoms per workgroup (one per lane)
+constexpr int kGradLanes = 64;          // lanes of a wave
 constexpr int kGradTile = 256;          // grid points staged per round
 constexpr double kGradDMin2 = 1.0e-4;   // D_MIN^2 (D_MIN = 0.01 A)
 
-template <int NV>
+template <int NV, int A>
 __global__ __launch_bounds__(kGradThreads) void k_sfe_grad(
     const double4* __restrict__ atoms, const double2* __restrict__ lj, int n_atoms,
     const float* __restrict__ g, int nx, int ny, size_t N, double dr, SiteConsts sc,
-    double* __restrict__ out, double scale) {
+    double* __restrict__ out, double scale, int lanes) {
   __shared__ double s_xyz[3][kGradTile];
   __shared__ double s_rg[NV][kGradTile];
   __shared__ double s_gc[kGradTile];
   __shared__ int s_live[kGradTile];
-  __shared__ double s_red[kGradThreads / 64][kGradAtoms][3];
+  __shared__ double s_red[kGradThreads / 64][kGradLanes][3];
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const int atom = blockIdx.y * kGradAtoms + lane;
-  const int a_ld = atom < n_atoms ? atom : n_atoms - 1;   // idle lanes repeat the last atom
-  const double4 at = atoms[a_ld];
-  double a12[NV], b6[NV];
+  const int al = lane & (lanes - 1), sub = lane / lanes, subs = kGradLanes / lanes;
+  const int atom0 = blockIdx.y * lanes * A + al;   // this lane's atoms: atom0 + lanes i
+  double4 at[A];
+  double a12[A][NV], b6[A][NV], gr[A][3];
 #pragma unroll
-  for (int s = 0; s < NV; ++s) {
-    const double2 c = lj[(size_t)a_ld * NV + s];
-    a12[s] = 12.0 * c.x;
-    b6[s] = 6.0 * c.y;
+  for (int i = 0; i < A; ++i) {
+    const int a = atom0 + lanes * i;
+    const int a_ld = a < n_atoms ? a : n_atoms - 1;   // idle lanes repeat the last atom
+    at[i] = atoms[a_ld];
+    gr[i][0] = gr[i][1] = gr[i][2] = 0.0;
+#pragma unroll
+    for (int s = 0; s < NV; ++s) {
+      const double2 c = lj[(size_t)a_ld * NV + s];
+      a12[i][s] = 12.0 * c.x;
+      b6[i][s] = 6.0 * c.y;
+    }
   }
-  double gx = 0.0, gy = 0.0, gz = 0.0;
 
   const size_t tiles = (N + kGradTile - 1) / kGradTile;
   for (size_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
@@ -85,57 +98,76 @@ __global__ __launch_bounds__(kGradThreads) void k_sfe_grad(
       s_live[t] = live;
     }
     __syncthreads();
-    for (int t = wave; t < cnt; t += kGradThreads / 64) {
-      if (!s_live[t]) continue;   // the same point for every lane of the wave
-      const double dx = s_xyz[0][t] - at.x, dy = s_xyz[1][t] - at.y, dz = s_xyz[2][t] - at.z;
-      const double d2 = dx * dx + dy * dy + dz * dz;
-      if (d2 < kGradDMin2) continue;
-      const double inv = 1.0 / sqrt(d2);
-      const double inv2 = inv * inv;
-      const double inv6 = inv2 * inv2 * inv2;
-      double sa = 0.0, sb = 0.0;
+    for (int t = wave * subs + sub; t < cnt; t += kGradThreads / lanes) {
+      if (!s_live[t]) continue;
+      const double x = s_xyz[0][t], y = s_xyz[1][t], z = s_xyz[2][t], gc = s_gc[t];
+      double rg[NV];
 #pragma unroll
-      for (int s = 0; s < NV; ++s) {
-        const double rg = s_rg[s][t];
-        sa += a12[s] * rg;
-        sb += b6[s] * rg;
+      for (int s = 0; s < NV; ++s) rg[s] = s_rg[s][t];
+#pragma unroll
+      for (int i = 0; i < A; ++i) {
+        const double dx = x - at[i].x, dy = y - at[i].y, dz = z - at[i].z;
+        const double d2 = dx * dx + dy * dy + dz * dz;
+        const double inv = rsqrt_nr(fmax(d2, kGradDMin2));
+        const double inv2 = inv * inv;
+        const double inv6 = inv2 * inv2 * inv2;
+        double sa = 0.0, sb = 0.0;
+#pragma unroll
+        for (int s = 0; s < NV; ++s) {
+          sa += a12[i][s] * rg[s];
+          sb += b6[i][s] * rg[s];
+        }
+        // S summed over sites with the weights rho_g g_g; the gradient adds S (R - r)
+        double S = -at[i].w * gc * inv2 * inv - inv6 * inv2 * (inv6 * sa - sb);
+        S = d2 < kGradDMin2 ? 0.0 : S;   // the potential is constant there
+        gr[i][0] -= S * dx;
+        gr[i][1] -= S * dy;
+        gr[i][2] -= S * dz;
       }
-      // S summed over sites with the weights rho_g g_g; the gradient adds S (R - r)
-      const double S = -at.w * s_gc[t] * inv2 * inv - inv6 * inv2 * (inv6 * sa - sb);
-      gx -= S * dx;
-      gy -= S * dy;
-      gz -= S * dz;
     }
   }
 
-  s_red[wave][lane][0] = gx;
-  s_red[wave][lane][1] = gy;
-  s_red[wave][lane][2] = gz;
-  __syncthreads();
-  if (wave == 0 && atom < n_atoms) {
-    double r[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      double v = s_red[0][lane][c];
+  for (int i = 0; i < A; ++i) {
+    const int atom = atom0 + lanes * i;
+    __syncthreads();   // the previous atoms' sums are read
 #pragma unroll
-      for (int w = 1; w < kGradThreads / 64; ++w) v += s_red[w][lane][c];
-      r[c] = v * scale;
+    for (int c = 0; c < 3; ++c) s_red[wave][lane][c] = gr[i][c];
+    __syncthreads();
+    if (wave == 0 && sub == 0 && atom < n_atoms) {
+      double* o = out + ((size_t)blockIdx.x * n_atoms + atom) * 3;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        double v = 0.0;
+        for (int w = 0; w < kGradThreads / 64; ++w)
+          for (int k = 0; k < subs; ++k) v += s_red[w][k * lanes + al][c];
+        o[c] = v * scale;
+      }
     }
-    double* o = out + ((size_t)blockIdx.x * n_atoms + atom) * 3;
-    o[0] = r[0];
-    o[1] = r[1];
-    o[2] = r[2];
   }
 }
 
-// out[i] = sum over the nb partial rows of part[b][i], in row order.
-__global__ void k_sfe_grad_reduce(const double* __restrict__ part, int nb, int n3,
-                                  double* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n3) return;
+// out[i] = sum over the nb partial rows of part[b][i].  A workgroup takes
+// kGradRedCols columns; thread group r of kGradRedRows adds rows r, r + kGradRedRows, ...
+// in row order and the groups are added in order (fixed, so deterministic).
+// Bound by the latency of a thread's loads in turn: 126 us for 512 rows x 600
+// columns with one thread per column, 21 us with 16.
+constexpr int kGradRedCols = 16, kGradRedRows = 16;
+
+__global__ __launch_bounds__(kGradRedCols* kGradRedRows) void k_sfe_grad_reduce(
+    const double* __restrict__ part, int nb, int n3, double* __restrict__ out) {
+  __shared__ double red[kGradRedRows][kGradRedCols];
+  const int c = threadIdx.x % kGradRedCols, r = threadIdx.x / kGradRedCols;
+  const int i = blockIdx.x * kGradRedCols + c;
   double v = 0.0;
-  for (int b = 0; b < nb; ++b) v += part[(size_t)b * n3 + i];
-  out[i] = v;
+  if (i < n3)
+    for (int b = r; b < nb; b += kGradRedRows) v += part[(size_t)b * n3 + i];
+  red[r][c] = v;
+  __syncthreads();
+  if (r == 0 && i < n3) {
+    for (int k = 1; k < kGradRedRows; ++k) v += red[k][c];
+    out[i] = v;
+  }
 }
 
 }  // namespace rism

@@ -1279,16 +1279,23 @@ __global__ void k_tune_state(IterState* st, int M, float eta) {
   st->hold = 0;
 }
 
+// Atoms per lane and lanes per point of the free-energy gradient: two atoms a
+// lane as soon as one a lane would not hold them all (200 atoms at 128^3: 765 us
+// with one, 690 with two; 24 atoms: 285 with one, 381 with two half-empty ones),
+// and half or a quarter of a wave per point where that many lanes hold them.
+constexpr int grad_atoms_per_lane(int n_atoms) { return n_atoms > kGradLanes ? 2 : 1; }
+constexpr int grad_lanes(int n_atoms) { return n_atoms > 32 ? 64 : n_atoms > 16 ? 32 : 16; }
+
 template <int NV>
 void launch_sfe_grad_nv(const Layout& L, const void* ws, const float* g, double dr,
-                        const SiteConsts& sc, double scale, unsigned nb, double* dst,
+                        const SiteConsts& sc, double scale, dim3 grid, double* dst,
                         hipStream_t s) {
-  const dim3 grid(nb, (unsigned)((L.n_atoms + kGradAtoms - 1) / kGradAtoms));
+  auto kernel = grad_atoms_per_lane(L.n_atoms) == 2 ? &k_sfe_grad<NV, 2> : &k_sfe_grad<NV, 1>;
   TIMED(F_SFEGRAD, s);
-  hipLaunchKernelGGL(k_sfe_grad<NV>, grid, dim3(kGradThreads), 0, s,
+  hipLaunchKernelGGL(kernel, grid, dim3(kGradThreads), 0, s,
                      at<double4>(const_cast<void*>(ws), L.off_atoms),
                      at<double2>(const_cast<void*>(ws), L.off_lj), L.n_atoms, g, L.nx, L.ny, L.N,
-                     dr, sc, dst, scale);
+                     dr, sc, dst, scale, grad_lanes(L.n_atoms));
 }
 
 // The shifted 3D transform of rism3d_transform with its twiddle tables in ws
@@ -1552,7 +1559,8 @@ rism3d_status rism3d_sfe_gradient(const rism3d_problem* pr, const rism3d_opts* o
   // spectrum section (scratch between iterations).  About 2048 workgroups in
   // all; a single column writes the result directly.
   const size_t tiles = (L.N + kGradTile - 1) / kGradTile;
-  const size_t chunks = (L.n_atoms + kGradAtoms - 1) / kGradAtoms;
+  const size_t per = (size_t)grad_lanes(L.n_atoms) * grad_atoms_per_lane(L.n_atoms);
+  const size_t chunks = (L.n_atoms + per - 1) / per;
   size_t nb = std::max<size_t>(1, 2048 / chunks);
   nb = std::min(nb, tiles);
   const size_t row = (size_t)L.n_atoms * 3 * sizeof(double);
@@ -1561,21 +1569,22 @@ rism3d_status rism3d_sfe_gradient(const rism3d_problem* pr, const rism3d_opts* o
   const SiteConsts sc = site_consts(pr, L.beta);
   const double scale = L.dv / L.beta;   // k_B T dV
   double* dst = nb == 1 ? grad : at<double>(ws, L.off_spec);
+  const dim3 grid((unsigned)nb, (unsigned)chunks);
   switch (L.nv) {
-    case 1: launch_sfe_grad_nv<1>(L, ws, g, pr->spacing, sc, scale, (unsigned)nb, dst, s); break;
-    case 2: launch_sfe_grad_nv<2>(L, ws, g, pr->spacing, sc, scale, (unsigned)nb, dst, s); break;
-    case 3: launch_sfe_grad_nv<3>(L, ws, g, pr->spacing, sc, scale, (unsigned)nb, dst, s); break;
-    case 4: launch_sfe_grad_nv<4>(L, ws, g, pr->spacing, sc, scale, (unsigned)nb, dst, s); break;
-    case 5: launch_sfe_grad_nv<5>(L, ws, g, pr->spacing, sc, scale, (unsigned)nb, dst, s); break;
-    case 6: launch_sfe_grad_nv<6>(L, ws, g, pr->spacing, sc, scale, (unsigned)nb, dst, s); break;
-    case 7: launch_sfe_grad_nv<7>(L, ws, g, pr->spacing, sc, scale, (unsigned)nb, dst, s); break;
-    default: launch_sfe_grad_nv<8>(L, ws, g, pr->spacing, sc, scale, (unsigned)nb, dst, s); break;
+    case 1: launch_sfe_grad_nv<1>(L, ws, g, pr->spacing, sc, scale, grid, dst, s); break;
+    case 2: launch_sfe_grad_nv<2>(L, ws, g, pr->spacing, sc, scale, grid, dst, s); break;
+    case 3: launch_sfe_grad_nv<3>(L, ws, g, pr->spacing, sc, scale, grid, dst, s); break;
+    case 4: launch_sfe_grad_nv<4>(L, ws, g, pr->spacing, sc, scale, grid, dst, s); break;
+    case 5: launch_sfe_grad_nv<5>(L, ws, g, pr->spacing, sc, scale, grid, dst, s); break;
+    case 6: launch_sfe_grad_nv<6>(L, ws, g, pr->spacing, sc, scale, grid, dst, s); break;
+    case 7: launch_sfe_grad_nv<7>(L, ws, g, pr->spacing, sc, scale, grid, dst, s); break;
+    default: launch_sfe_grad_nv<8>(L, ws, g, pr->spacing, sc, scale, grid, dst, s); break;
   }
   LAUNCH_CHECK();
   if (nb > 1) {
     const int n3 = L.n_atoms * 3;
-    hipLaunchKernelGGL(k_sfe_grad_reduce, dim3(blocks_for(n3, 256)), dim3(256), 0, s, dst, (int)nb,
-                       n3, grad);
+    hipLaunchKernelGGL(k_sfe_grad_reduce, dim3(blocks_for(n3, kGradRedCols)),
+                       dim3(kGradRedCols * kGradRedRows), 0, s, dst, (int)nb, n3, grad);
     LAUNCH_CHECK();
   }
   if (g_timer.on) {

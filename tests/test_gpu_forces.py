@@ -57,6 +57,18 @@ def test_gradient_on_a_given_distribution(R, O, case):
     assert err <= 1e-10 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("n_atoms", [16, 17, 32, 33, 64, 65, 129])
+def test_gradient_at_the_lane_splits(R, O, n_atoms):
+    """Atom counts on both sides of every split of a wave's lanes (16 and 32
+    lanes a point, one and two atoms a lane); bar as for a given distribution."""
+    prob = inputs.small_problem(55, n_atoms=n_atoms, shape=(18, 16, 20), radius=6.0)
+    s, _, _ = _solver(R, prob)
+    g = inputs.synthetic_distribution(prob, 55, exclusion=1.0)
+    got = s.sfe_gradient(torch.tensor(g, device="cuda")).cpu().numpy()
+    ref = O.sfe_gradient(prob, g.astype(np.float64))
+    assert np.abs(got - ref).max() <= 1e-10 * np.abs(ref).max()
+
+
 def test_atom_on_a_grid_point(R, O):
     """The pair inside the 0.01 A clamp adds nothing on either side."""
     prob = inputs.small_problem(3, n_atoms=2, shape=(16, 16, 16), radius=1.5)
