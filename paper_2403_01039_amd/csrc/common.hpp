@@ -21,7 +21,6 @@ static_assert(kScreen == 1.0, "the potential kernel evaluates (1 - e^{-d/l})/d w
 constexpr int kMaxSites = RISM3D_MAX_SITES;
 constexpr int kMaxDepth = RISM3D_MAX_DEPTH;
 constexpr int kHistLen = RISM3D_HISTORY_LEN;
-constexpr int kMaxRadixPasses = 12;
 
 // Solvent-site constants passed by value to kernels.
 struct SiteConsts {
@@ -42,13 +41,6 @@ struct GramW {
 struct SiteLJ {
   double sigma[kMaxSites];
   double eps[kMaxSites];
-};
-
-// An FFT axis: length and radix plan (product of radices == n).
-struct AxisPlan {
-  int n;
-  int npass;
-  int radix[kMaxRadixPasses];
 };
 
 // Device-resident MDIIS / iteration state (one per workspace).

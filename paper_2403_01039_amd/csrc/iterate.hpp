@@ -101,12 +101,15 @@ __global__ void k_mark_prepared(IterState* st, unsigned layout_key) {
 // the anchor, with dg kept for the residual.  Two sites share one complex grid
 // (site 2p real part, site 2p+1 imaginary part).
 // ---------------------------------------------------------------------------
-// V consecutive floats (V = 4: one 16-byte access).
+// V consecutive floats (V = 4: one 16-byte access, V = 2: one of 8 bytes).
 template <int V>
 __device__ inline void ldv(const float* __restrict__ p, float* o) {
   if constexpr (V == 4) {
     const float4 t = *reinterpret_cast<const float4*>(p);
     o[0] = t.x; o[1] = t.y; o[2] = t.z; o[3] = t.w;
+  } else if constexpr (V == 2) {
+    const float2 t = *reinterpret_cast<const float2*>(p);
+    o[0] = t.x; o[1] = t.y;
   } else {
 #pragma unroll
     for (int i = 0; i < V; ++i) o[i] = p[i];
@@ -116,6 +119,8 @@ template <int V>
 __device__ inline void stv(float* __restrict__ p, const float* v) {
   if constexpr (V == 4) {
     *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+  } else if constexpr (V == 2) {
+    *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
   } else {
 #pragma unroll
     for (int i = 0; i < V; ++i) p[i] = v[i];
@@ -225,46 +230,6 @@ __device__ inline void update_points(const UpdateCtl& u, float* __restrict__ tau
         o32[s][v] = dg[v] - tau[v];
       }
       stv<V>(dg_out + gn, dg);
-    }
-  }
-}
-
-template <bool ANCHOR, int V>
-__global__ __launch_bounds__(kElemThreads) void k_update_closure(
-    const IterState* __restrict__ st, float* __restrict__ tau_hist,
-    const float* __restrict__ res_hist, const float* __restrict__ w,
-    const float* __restrict__ tau_ref, const float* __restrict__ tau_lo,
-    const float* __restrict__ dref, float* __restrict__ dg_out, void* __restrict__ spec, size_t N,
-    int nv, int npair, int M, int kind, int order) {
-  if (skip_iteration<ANCHOR>(st->done)) return;
-  const size_t NQ = N / V;
-  const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= (size_t)npair * NQ) return;
-  const int p = (int)(q / NQ);
-  const size_t n = (q - (size_t)p * NQ) * V;
-  const UpdateCtl u = load_update_ctl(st, M);
-  double o64[2][V];
-  float o32[2][V];
-  update_points<ANCHOR, V>(u, tau_hist, res_hist, w, tau_ref, tau_lo, dref, dg_out, N, nv, p, n,
-                           kind, order, o64, o32);
-  const size_t o = (size_t)p * N + n;
-  if (ANCHOR) {
-    double2* sp = static_cast<double2*>(spec) + o;
-#pragma unroll
-    for (int v = 0; v < V; ++v) sp[v] = make_double2(o64[0][v], o64[1][v]);
-  } else {
-    float* sp = reinterpret_cast<float*>(static_cast<float2*>(spec) + o);
-    float pk[2 * V];
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-      pk[2 * v] = o32[0][v];
-      pk[2 * v + 1] = o32[1][v];
-    }
-    if constexpr (V == 4) {
-      stv<4>(sp, pk);
-      stv<4>(sp + 4, pk + 4);
-    } else {
-      stv<2 * V>(sp, pk);
     }
   }
 }

@@ -20,6 +20,7 @@
 #include "fft.hpp"
 #include "iterate.hpp"
 #include "forces.hpp"
+#include "flex.hpp"
 #include "fused.hpp"
 #include "setup.hpp"
 #include "unet.hpp"
@@ -183,20 +184,103 @@ struct TimedScope {
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
-bool plan_axis(int n, AxisPlan* p) {
-  if (n < 2 || n > kFftMaxN) return false;
-  p->n = n;
-  p->npass = 0;
-  int m = n;
-  const int radices[5] = {8, 4, 2, 3, 5};
-  for (int r : radices) {
-    while (m % r == 0) {
-      if (p->npass >= kMaxRadixPasses) return false;
-      p->radix[p->npass++] = r;
-      m /= r;
-    }
+// The trips of a list of radices: as few as possible, and among those the ones
+// that allow the largest tile.
+void plan_trips(const int* r, int n_r, int cap, FlexPlan* best, FlexPlan* cur) {
+  if (n_r == 0) {
+    if (cur->np > best->np || (cur->np == best->np && cap <= best->cap)) return;
+    best->np = cur->np;
+    best->cap = cap;
+    std::copy(cur->ra, cur->ra + cur->np, best->ra);
+    std::copy(cur->rb, cur->rb + cur->np, best->rb);
+    return;
   }
-  return m == 1;
+  if (cur->np >= kFlexMaxPass) return;
+  for (int two = 0; two < 2; ++two) {
+    if (two && (n_r < 2 || !flex_pair(r[0], r[1]))) continue;
+    cur->ra[cur->np] = r[0];
+    cur->rb[cur->np] = two ? r[1] : 1;
+    const int R = cur->ra[cur->np] * cur->rb[cur->np];
+    ++cur->np;
+    plan_trips(r + 1 + two, n_r - 1 - two, std::min(cap, kFftThreads * R * flex_held(R)), best, cur);
+    --cur->np;
+  }
+}
+
+// The plan of length n; false unless 2..512 with prime factors 2, 3 and 5.
+bool plan_axis(int n, FlexPlan* p) {
+  if (n < 2 || n > kFftMaxN) return false;
+  int r[10], n_r = 0, m = n;
+  for (int f : {8, 4, 2, 3, 5})
+    for (; m % f == 0; m /= f) r[n_r++] = f;
+  if (m != 1) return false;
+  memset(p, 0, sizeof(*p));
+  FlexPlan cur = *p;
+  p->np = kFlexMaxPass + 1;
+  plan_trips(r, n_r, 1 << 20, p, &cur);
+  p->n = n;
+  p->pitch = n + n / 8 + 1;
+  p->inv_n = 1.0f / (float)n;
+  int ns = 1;
+  for (int i = 0; i < p->np; ++i) {
+    const int R = p->ra[i] * p->rb[i];
+    p->ns[i] = ns;
+    p->nb[i] = n / R;
+    p->sa[i] = 2 * n / (ns * p->ra[i]);
+    p->sb[i] = 2 * n / (ns * R);
+    p->inv_nb[i] = 1.0f / (float)p->nb[i];
+    p->inv_ns[i] = 1.0f / (float)ns;
+    ns *= R;
+  }
+  return true;
+}
+
+// Tiles of the flexible transforms (elem bytes a value), from sweeps over
+// 120 x 100 x 90, 160 x 120 x 90, 54 x 50 x 48, 80 x 144 x 100 and 144 x 160 x 160:
+// a tile that the plan's registers transform in one go, in at most 32 KB of LDS.
+constexpr size_t kFlexTileBytes = 32768;
+
+// Rows per workgroup: about 1024 workgroups, but at least 8 rows each (2880
+// workgroups of 4 rows take 17.1 us on 120-point rows, 17 rows 11.1).
+int flex_rows(const FlexPlan& P, size_t elem, size_t rows) {
+  size_t l = std::min<size_t>(P.cap / P.n, kFlexTileBytes / (P.pitch * elem));
+  l = std::min(l, std::max<size_t>(8, rows / 1024));
+  return (int)std::max<size_t>(l, 1);
+}
+
+// Rows per workgroup of the update: smaller tiles, since its history loads and
+// not the transform want workgroups in flight (120 points: 8 rows 29.8 us, 17
+// rows 32.5; 80 points: 12 rows 49.2, 24 rows 50.9).
+int flex_update_rows(const FlexPlan& P, size_t elem, size_t rows) {
+  return std::min(flex_rows(P, elem, rows), std::max(4, 1024 / P.n));
+}
+
+// Columns per workgroup: whole 128-byte segments of FP32 pairs, 16, 24 or 32,
+// whichever pads nx least (120: 24 columns 11.9 us, 30 columns 14.9, 16 13.6;
+// 160: 16 columns 20.1, 32 26.2).
+int flex_cols(const FlexPlan& P, size_t elem, int nx) {
+  const int most = (int)std::min<size_t>(P.cap / P.n, kFlexTileBytes / (P.pitch * elem));
+  int best = std::max(1, std::min(most, 16) & ~1);
+  for (int l : {24, 32})
+    if (l <= most && (nx + l - 1) / l * l < (nx + best - 1) / best * best) best = l;
+  return best;
+}
+
+size_t flex_lds(const FlexPlan& P, int lines, size_t elem) {
+  return ((size_t)lines * P.pitch + 2 * P.n) * elem;
+}
+
+// Columns per side and workgroup of the flexible z kernel (even, at most 8): what
+// the registers take in one go, and at least 512 workgroups (120 x 100 x 90, 3
+// sites: 8 columns 17.3 us, 12 22.5; 160 x 120 x 90, 5 sites: 4 columns 38.2, 8
+// 43.4).  0: two columns do not fit the LDS.
+int flex_zcols(const FlexPlan& P, size_t elem, int npair, int nx, int ny) {
+  int b = std::min(8, P.cap / (2 * npair * P.n)) & ~1;
+  while (b > 2 && (flex_lds(P, 2 * npair * b, elem) > (size_t)kFlexMaxLds ||
+                   (size_t)(ny / 2) * ((nx + b - 1) / b) < 512))
+    b -= 2;
+  b = std::max(b, 2);
+  return flex_lds(P, 2 * npair * b, elem) <= (size_t)kFlexMaxLds ? b : 0;
 }
 
 double axis_kmax(int n, double dk) {
@@ -213,7 +297,7 @@ struct Layout {
   GramW gw;   // Gram inner-product weights (1, or 1/rho for modified Anderson)
   size_t N, half;
   double dkx, dky, dkz, beta, dv;
-  AxisPlan px, py, pz;
+  FlexPlan px, py, pz;
   size_t off_state, off_w, off_phi, off_F, off_tau, off_res, off_tref, off_tlo, off_rref, off_dref,
       off_dg,
       off_spec,
@@ -591,7 +675,7 @@ template <typename C>
 void launch_axis(const Layout& L, C* spec, const C* const tw[3], int axis, int forward,
                  const int* done, hipStream_t s, Batch bt = {}) {
   const bool f64 = std::is_same<C, double2>::value;
-  const AxisPlan& p = axis == 0 ? L.px : (axis == 1 ? L.py : L.pz);
+  const FlexPlan& p = axis == 0 ? L.px : (axis == 1 ? L.py : L.pz);
   TIMED((f64 ? F_FFTX64 : F_FFTX32) + axis, s);
   bool ok = false;
   if (fixed_fft_size(p.n)) {
@@ -600,18 +684,14 @@ void launch_axis(const Layout& L, C* spec, const C* const tw[3], int axis, int f
     else ok = launch_fixed_axis<C, 2>(p.n, L, spec, tw[axis], forward, done, s, bt);
   }
   if (ok) return;   // batches only reach here with fixed-size lengths (batch_plan)
-  const int lines = fft_lines_per_block<C>(axis, p.n, L.nx);
-  unsigned grid;
-  if (axis == 0) {
-    const size_t rows = (size_t)L.npair * L.nz * L.ny;
-    grid = (unsigned)((rows + lines - 1) / lines);
-  } else {
-    const int tiles_x = (L.nx + lines - 1) / lines;
-    const int outer = axis == 1 ? L.npair * L.nz : L.npair * L.ny;
-    grid = (unsigned)outer * tiles_x;
-  }
-  hipLaunchKernelGGL(k_fft_axis<C>, dim3(grid), dim3(kFftThreads), 0, s, spec, L.nx, L.ny, L.nz,
-                     L.npair, axis, p, tw[axis], forward, lines, done);
+  const size_t rows = (size_t)L.npair * L.nz * L.ny;
+  const int lines = axis == 0 ? flex_rows(p, sizeof(C), rows) : flex_cols(p, sizeof(C), L.nx);
+  const unsigned grid =
+      axis == 0 ? (unsigned)((rows + lines - 1) / lines)
+                : (unsigned)(L.npair * (axis == 1 ? L.nz : L.ny)) * ((L.nx + lines - 1) / lines);
+  auto kernel = L.nx % 2 == 0 && ((uintptr_t)spec & 15) == 0 ? &k_flex_axis<C, 2> : &k_flex_axis<C, 1>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kFftThreads), flex_lds(p, lines, sizeof(C)), s, spec,
+                     L.nx, L.ny, L.nz, L.npair, axis, p, tw[axis], forward, lines, done);
 }
 
 // Forward (forward != 0) or inverse 3D transform of all packed pairs, one
@@ -712,6 +792,18 @@ void launch_zcz(const Layout& L, void* ws, double inv_dkt, const int* done, hipS
   }
 }
 
+// The control step after a residual kernel of nblk workgroups.
+void launch_control(const Layout& L, void* ws, const rism3d_opts* op, bool anchor, unsigned nblk,
+                    hipStream_t s, Batch bt) {
+  TIMED(F_CONTROL, s);
+  const double inv_count = 1.0 / ((double)L.N * (double)L.nv);
+  hipLaunchKernelGGL(L.M <= 5 ? &k_control<5> : &k_control<kMaxDepth>, dim3(1, bt.nb),
+                     dim3(kCtlThreads), 0, s, at<IterState>(ws, L.off_state),
+                     at<double>(ws, L.off_part), (int)nblk, L.M, inv_count, op->tol, op->max_iter,
+                     (float)op->mdiis_eta, op->eta_dynamic, (int)op->accelerator, op->anderson_s1,
+                     op->anderson_s2, anchor ? 1 : 0, at<double2>(ws, L.off_hist), bt.stride);
+}
+
 // Fused first and last kernels of an iteration (x-axis transform fused with the
 // update+closure and with the residual+Gram+control).
 template <bool ANCHOR, int N, int LINES = fixed_lines<PrecC<ANCHOR>, N, 0>()>
@@ -755,15 +847,7 @@ void launch_fused_l(const Layout& L, void* ws, const rism3d_opts* op, bool first
                          at<float>(ws, L.off_dg), L.ny, L.nz, L.nv, L.npair, L.M, kind, order, tw,
                          at<double>(ws, L.off_part), L.gw, bt.stride);
     }
-    if (!control) return;
-    TIMED(F_CONTROL, s);
-    const double inv_count = 1.0 / ((double)L.N * (double)L.nv);
-    hipLaunchKernelGGL(L.M <= 5 ? &k_control<5> : &k_control<kMaxDepth>, dim3(1, bt.nb),
-                       dim3(kCtlThreads), 0, s, st,
-                       at<double>(ws, L.off_part), (int)grid.x, L.M, inv_count, op->tol,
-                       op->max_iter, (float)op->mdiis_eta, op->eta_dynamic,
-                       (int)op->accelerator, op->anderson_s1, op->anderson_s2, ANCHOR ? 1 : 0,
-                       at<double2>(ws, L.off_hist), bt.stride);
+    if (control) launch_control(L, ws, op, ANCHOR, grid.x, s, bt);
   }
 }
 
@@ -808,6 +892,99 @@ void launch_fused(const Layout& L, void* ws, const rism3d_opts* op, bool first_h
   }
 }
 
+// First and last kernels of an iteration on x lengths without fixed kernels.
+template <bool ANCHOR, int V, int MM>
+void launch_flex_update(const Layout& L, void* ws, const rism3d_opts* op, hipStream_t s) {
+  using C = PrecC<ANCHOR>;
+  const int kind = (int)op->closure;
+  const int order = op->closure == RISM3D_PSE ? op->pse_order : 1;
+  const size_t rows = (size_t)L.npair * L.nz * L.ny;
+  const int lines = flex_update_rows(L.px, sizeof(C), rows);
+  TIMED(ANCHOR ? F_UPDFFT64 : F_UPDFFT32, s);
+  hipLaunchKernelGGL((k_flex_update<ANCHOR, V, MM>), dim3((unsigned)((rows + lines - 1) / lines)),
+                     dim3(kFftThreads), flex_lds(L.px, lines, sizeof(C)), s,
+                     at<IterState>(ws, L.off_state), at<float>(ws, L.off_tau),
+                     at<float>(ws, L.off_res), at<float>(ws, L.off_w), at<float>(ws, L.off_tref),
+                     at<float>(ws, L.off_tlo), at<float>(ws, L.off_dref), at<float>(ws, L.off_dg),
+                     at<void>(ws, L.off_spec), L.ny, L.nz, L.nv, L.npair, L.M, kind, order, L.px,
+                     lines, at<C>(ws, ANCHOR ? L.off_tw64[0] : L.off_tw32[0]));
+}
+
+template <bool ANCHOR, int V>
+void launch_residual(const Layout& L, void* ws, const rism3d_opts* op, unsigned nblk,
+                     hipStream_t s) {
+  TIMED(ANCHOR ? F_RESIDUAL64 : F_RESIDUAL32, s);
+  hipLaunchKernelGGL((k_residual<ANCHOR, V>), dim3(nblk), dim3(kRedThreads), 0, s,
+                     at<IterState>(ws, L.off_state), at<void>(ws, L.off_spec),
+                     at<float>(ws, L.off_w), at<float>(ws, L.off_tau), at<float>(ws, L.off_res),
+                     at<float>(ws, L.off_tref), at<float>(ws, L.off_tlo), at<float>(ws, L.off_rref),
+                     at<float>(ws, L.off_dref), at<float>(ws, L.off_dg), L.N, L.nv, L.npair, L.M,
+                     (int)op->closure, op->closure == RISM3D_PSE ? op->pse_order : 1,
+                     at<double>(ws, L.off_part), L.gw);
+}
+
+void launch_flex(const Layout& L, void* ws, const rism3d_opts* op, bool anchor, bool first_half,
+                 hipStream_t s) {
+  if (first_half) {
+    // rows of whole 16-byte vectors take four points a thread, others two (nx is even)
+    const bool v4 = L.nx % 4 == 0;
+    if (anchor) launch_flex_update<true, 2, kMaxDepth>(L, ws, op, s);
+    else if (L.M <= 5 && v4) launch_flex_update<false, 4, 5>(L, ws, op, s);
+    else if (L.M <= 5) launch_flex_update<false, 2, 5>(L, ws, op, s);
+    else if (v4) launch_flex_update<false, 4, kMaxDepth>(L, ws, op, s);
+    else launch_flex_update<false, 2, kMaxDepth>(L, ws, op, s);
+    return;
+  }
+  const int* done = &at<IterState>(ws, L.off_state)->done;
+  const float2* tw32[3] = {at<float2>(ws, L.off_tw32[0]), nullptr, nullptr};
+  const double2* tw64[3] = {at<double2>(ws, L.off_tw64[0]), nullptr, nullptr};
+  if (anchor) launch_axis(L, at<double2>(ws, L.off_spec), tw64, 0, 0, done, s);
+  else launch_axis(L, at<float2>(ws, L.off_spec), tw32, 0, 0, done, s);
+  const bool v4 = L.N % 4 == 0;
+  const unsigned nblk = std::min<unsigned>(
+      blocks_for((size_t)L.npair * (v4 ? L.N / 4 : L.N), kRedThreads), kRedBlocks);
+  if (anchor && v4) launch_residual<true, 4>(L, ws, op, nblk, s);
+  else if (anchor) launch_residual<true, 1>(L, ws, op, nblk, s);
+  else if (v4) launch_residual<false, 4>(L, ws, op, nblk, s);
+  else launch_residual<false, 1>(L, ws, op, nblk, s);
+  launch_control(L, ws, op, anchor, nblk, s, Batch{});
+}
+
+// z transform + contraction + inverse z transform of the lengths without fixed
+// kernels, as far as two columns a side fit the LDS.
+bool flex_zcz_supported(const Layout& L) {
+  return !fixed_fft_size(L.nz) && flex_zcols(L.pz, sizeof(double2), L.npair, L.nx, L.ny) > 0;
+}
+
+template <typename C, int NV>
+void launch_flex_zcz_nv(const Layout& L, void* ws, double inv_dkt, const int* done, hipStream_t s) {
+  constexpr bool F64 = std::is_same<C, double2>::value;
+  using S = typename ScalarOf<C>::type;
+  const int B = flex_zcols(L.pz, sizeof(C), L.npair, L.nx, L.ny);
+  const dim3 grid((unsigned)(L.ny / 2) * ((L.nx + B - 1) / B)), block(kFftThreads);
+  TIMED(F64 ? F_ZCZ64 : F_ZCZ32, s);
+  hipLaunchKernelGGL((k_flex_zcz<C, NV, F64>), grid, block,
+                     flex_lds(L.pz, 2 * L.npair * B, sizeof(C)), s, at<C>(ws, L.off_spec), L.nx, L.ny,
+                     L.pz, B, at<C>(ws, F64 ? L.off_tw64[2] : L.off_tw32[2]), L.dkx, L.dky, L.dkz,
+                     F64 ? at<C>(ws, L.off_F) : (const C*)nullptr,
+                     at<S>(ws, F64 ? L.off_chi64 : L.off_chi32),
+                     F64 ? at<S>(ws, L.off_q64) : (const S*)nullptr, inv_dkt, L.m_tab, done);
+}
+
+template <typename C>
+void launch_flex_zcz(const Layout& L, void* ws, double inv_dkt, const int* done, hipStream_t s) {
+  switch (L.nv) {
+    case 1: launch_flex_zcz_nv<C, 1>(L, ws, inv_dkt, done, s); break;
+    case 2: launch_flex_zcz_nv<C, 2>(L, ws, inv_dkt, done, s); break;
+    case 3: launch_flex_zcz_nv<C, 3>(L, ws, inv_dkt, done, s); break;
+    case 4: launch_flex_zcz_nv<C, 4>(L, ws, inv_dkt, done, s); break;
+    case 5: launch_flex_zcz_nv<C, 5>(L, ws, inv_dkt, done, s); break;
+    case 6: launch_flex_zcz_nv<C, 6>(L, ws, inv_dkt, done, s); break;
+    case 7: launch_flex_zcz_nv<C, 7>(L, ws, inv_dkt, done, s); break;
+    default: launch_flex_zcz_nv<C, 8>(L, ws, inv_dkt, done, s); break;
+  }
+}
+
 // One evaluation of the 3D-RISM map plus the MDIIS bookkeeping: update +
 // closure, forward FFT, contraction, inverse FFT, residual + Gram row, control.
 // anchor: FP64 evaluation that re-bases the FP32 increments.
@@ -815,87 +992,45 @@ void launch_iteration(const Layout& L, void* ws, const rism3d_opts* op, double i
                       bool anchor, hipStream_t s, Batch bt = {}) {
   IterState* st = at<IterState>(ws, L.off_state);
   const int* done = &st->done;
-  const int kind = (int)op->closure;
-  const int order = op->closure == RISM3D_PSE ? op->pse_order : 1;
-  if (fixed_fft_size(L.nx)) {
-    const int xl = anchor ? 0 : tune_for(L).x_lines;
-    if (anchor) launch_fused<true>(L, ws, op, true, s, bt);
-    else launch_fused<false>(L, ws, op, true, s, bt, xl);
-    if (zcz_supported(L)) {
-      // y pass, then z + contraction + z fused, then inverse y pass
-      const float2* tw32[3] = {at<float2>(ws, L.off_tw32[0]), at<float2>(ws, L.off_tw32[1]),
-                               at<float2>(ws, L.off_tw32[2])};
-      const double2* tw64[3] = {at<double2>(ws, L.off_tw64[0]), at<double2>(ws, L.off_tw64[1]),
-                                at<double2>(ws, L.off_tw64[2])};
-      if (anchor) {
-        launch_axis(L, at<double2>(ws, L.off_spec), tw64, 1, 1, done, s, bt);
-        launch_zcz<double2>(L, ws, inv_dkt, done, s, bt);
-        launch_axis(L, at<double2>(ws, L.off_spec), tw64, 1, 0, done, s, bt);
-      } else {
-        const Tune tn = tune_for(L);
-        if (!launch_y32(L, at<float2>(ws, L.off_spec), tw32[1], 1, done, s, bt, tn.y_lines))
-          launch_axis(L, at<float2>(ws, L.off_spec), tw32, 1, 1, done, s, bt);
-        launch_zcz<float2>(L, ws, inv_dkt, done, s, bt, tn.z_cols);
-        if (!launch_y32(L, at<float2>(ws, L.off_spec), tw32[1], 0, done, s, bt, tn.y_lines))
-          launch_axis(L, at<float2>(ws, L.off_spec), tw32, 1, 0, done, s, bt);
-      }
+  const bool fixed_x = fixed_fft_size(L.nx);
+  const int xl = anchor ? 0 : tune_for(L).x_lines;
+  if (!fixed_x) launch_flex(L, ws, op, anchor, true, s);
+  else if (anchor) launch_fused<true>(L, ws, op, true, s, bt);
+  else launch_fused<false>(L, ws, op, true, s, bt, xl);
+  // (a fixed z length behind other x lengths keeps its separate passes, whose
+  // roundings differ from the fused kernel's)
+  const bool fixed_z = fixed_x && zcz_supported(L);
+  const bool flex_z = !fixed_z && flex_zcz_supported(L);
+  if (fixed_z || flex_z) {
+    // y pass, then z + contraction + z fused, then inverse y pass
+    const float2* tw32[3] = {at<float2>(ws, L.off_tw32[0]), at<float2>(ws, L.off_tw32[1]),
+                             at<float2>(ws, L.off_tw32[2])};
+    const double2* tw64[3] = {at<double2>(ws, L.off_tw64[0]), at<double2>(ws, L.off_tw64[1]),
+                              at<double2>(ws, L.off_tw64[2])};
+    if (anchor) {
+      launch_axis(L, at<double2>(ws, L.off_spec), tw64, 1, 1, done, s, bt);
+      if (flex_z) launch_flex_zcz<double2>(L, ws, inv_dkt, done, s);
+      else launch_zcz<double2>(L, ws, inv_dkt, done, s, bt);
+      launch_axis(L, at<double2>(ws, L.off_spec), tw64, 1, 0, done, s, bt);
     } else {
-      if (anchor) launch_fft3<double2>(L, ws, 1, done, s, true);
-      else launch_fft3<float2>(L, ws, 1, done, s, true);
-      launch_contract(L, ws, anchor, inv_dkt, done, s);
-      if (anchor) launch_fft3<double2>(L, ws, 0, done, s, true);
-      else launch_fft3<float2>(L, ws, 0, done, s, true);
+      const Tune tn = tune_for(L);
+      if (!launch_y32(L, at<float2>(ws, L.off_spec), tw32[1], 1, done, s, bt, tn.y_lines))
+        launch_axis(L, at<float2>(ws, L.off_spec), tw32, 1, 1, done, s, bt);
+      if (flex_z) launch_flex_zcz<float2>(L, ws, inv_dkt, done, s);
+      else launch_zcz<float2>(L, ws, inv_dkt, done, s, bt, tn.z_cols);
+      if (!launch_y32(L, at<float2>(ws, L.off_spec), tw32[1], 0, done, s, bt, tn.y_lines))
+        launch_axis(L, at<float2>(ws, L.off_spec), tw32, 1, 0, done, s, bt);
     }
-    if (anchor) launch_fused<true>(L, ws, op, false, s, bt);
-    else launch_fused<false>(L, ws, op, false, s, bt, xl);
-    return;
+  } else {
+    if (anchor) launch_fft3<double2>(L, ws, 1, done, s, true);
+    else launch_fft3<float2>(L, ws, 1, done, s, true);
+    launch_contract(L, ws, anchor, inv_dkt, done, s);
+    if (anchor) launch_fft3<double2>(L, ws, 0, done, s, true);
+    else launch_fft3<float2>(L, ws, 0, done, s, true);
   }
-  const bool v4 = (L.N % 4) == 0;
-  const size_t quads = (size_t)L.npair * (v4 ? L.N / 4 : L.N);
-  const dim3 eg(blocks_for(quads, kElemThreads)), eb(kElemThreads);
-#define RISM_UPDATE_ARGS                                                                    \
-  st, at<float>(ws, L.off_tau), at<float>(ws, L.off_res), at<float>(ws, L.off_w),     \
-      at<float>(ws, L.off_tref), at<float>(ws, L.off_tlo), at<float>(ws, L.off_dref),         \
-      at<float>(ws, L.off_dg), at<void>(ws, L.off_spec), L.N, L.nv, L.npair, L.M, kind, order
-  {
-    TIMED(anchor ? F_UPDATE64 : F_UPDATE32, s);
-    if (anchor && v4) hipLaunchKernelGGL((k_update_closure<true, 4>), eg, eb, 0, s, RISM_UPDATE_ARGS);
-    else if (anchor) hipLaunchKernelGGL((k_update_closure<true, 1>), eg, eb, 0, s, RISM_UPDATE_ARGS);
-    else if (v4) hipLaunchKernelGGL((k_update_closure<false, 4>), eg, eb, 0, s, RISM_UPDATE_ARGS);
-    else hipLaunchKernelGGL((k_update_closure<false, 1>), eg, eb, 0, s, RISM_UPDATE_ARGS);
-  }
-#undef RISM_UPDATE_ARGS
-  if (anchor) launch_fft3<double2>(L, ws, 1, done, s);
-  else launch_fft3<float2>(L, ws, 1, done, s);
-  launch_contract(L, ws, anchor, inv_dkt, done, s);
-  if (anchor) launch_fft3<double2>(L, ws, 0, done, s);
-  else launch_fft3<float2>(L, ws, 0, done, s);
-  unsigned nblk = blocks_for(quads, kRedThreads);
-  if (nblk > (unsigned)kRedBlocks) nblk = kRedBlocks;
-#define RISM_RESID_ARGS                                                                       \
-  st, at<void>(ws, L.off_spec), at<float>(ws, L.off_w), at<float>(ws, L.off_tau),             \
-      at<float>(ws, L.off_res), at<float>(ws, L.off_tref), at<float>(ws, L.off_tlo),          \
-      at<float>(ws, L.off_rref), at<float>(ws, L.off_dref), at<float>(ws, L.off_dg), L.N, L.nv,  \
-      L.npair, L.M, kind, order,                                                                \
-      at<double>(ws, L.off_part), L.gw
-  {
-    TIMED(anchor ? F_RESIDUAL64 : F_RESIDUAL32, s);
-    const dim3 rg(nblk), rb(kRedThreads);
-    if (anchor && v4) hipLaunchKernelGGL((k_residual<true, 4>), rg, rb, 0, s, RISM_RESID_ARGS);
-    else if (anchor) hipLaunchKernelGGL((k_residual<true, 1>), rg, rb, 0, s, RISM_RESID_ARGS);
-    else if (v4) hipLaunchKernelGGL((k_residual<false, 4>), rg, rb, 0, s, RISM_RESID_ARGS);
-    else hipLaunchKernelGGL((k_residual<false, 1>), rg, rb, 0, s, RISM_RESID_ARGS);
-  }
-#undef RISM_RESID_ARGS
-  const double inv_count = 1.0 / ((double)L.N * (double)L.nv);
-  {
-    TIMED(F_CONTROL, s);
-    hipLaunchKernelGGL(L.M <= 5 ? &k_control<5> : &k_control<kMaxDepth>, dim3(1),
-                       dim3(kCtlThreads), 0, s, st, at<double>(ws, L.off_part),
-                       (int)nblk, L.M, inv_count, op->tol, op->max_iter, (float)op->mdiis_eta,
-                       op->eta_dynamic, (int)op->accelerator, op->anderson_s1, op->anderson_s2,
-                       anchor ? 1 : 0, at<double2>(ws, L.off_hist), (size_t)0);
-  }
+  if (!fixed_x) launch_flex(L, ws, op, anchor, false, s);
+  else if (anchor) launch_fused<true>(L, ws, op, false, s, bt);
+  else launch_fused<false>(L, ws, op, false, s, bt, xl);
 }
 
 int order_of(const rism3d_opts* op) { return op->closure == RISM3D_PSE ? op->pse_order : 1; }
@@ -1055,8 +1190,8 @@ rism3d_status prepare(const rism3d_problem* pr, const Layout& L, void* ws, hipSt
   {
     TIMED(F_FTILDE, s);
     hipLaunchKernelGGL(k_ftilde,
-                       dim3(blocks_for((size_t)(L.nz / 2) * L.ny, kFtRows),
-                            blocks_for(L.nx, kFtCols)),
+                       dim3(blocks_for(L.nx, kFtCols), blocks_for(L.ny, kFtRows),
+                            blocks_for(L.nz / 2, kFtZ)),
                        dim3(256), 0, s,
                        at<double2>(ws, L.off_ph), at<double4>(ws, L.off_atoms), L.n_atoms, L.nx, L.ny,
                        L.nz, L.dkx, L.dky, L.dkz, pref, at<double2>(ws, L.off_F));
@@ -1903,7 +2038,7 @@ rism3d_status rism3d_get_potential(const rism3d_problem* pr, const rism3d_opts* 
 }
 
 size_t rism3d_transform_workspace_bytes(int nx, int ny, int nz) {
-  AxisPlan p;
+  FlexPlan p;
   if (!plan_axis(nx, &p) || !plan_axis(ny, &p) || !plan_axis(nz, &p)) {
     fail(RISM3D_E_ARG, "grid %dx%dx%d unsupported", nx, ny, nz);
     return 0;
@@ -1914,7 +2049,7 @@ size_t rism3d_transform_workspace_bytes(int nx, int ny, int nz) {
 
 rism3d_status rism3d_transform(int nx, int ny, int nz, int count, void* d_data, int forward,
                                void* ws, size_t ws_bytes, hipStream_t s) {
-  AxisPlan p;
+  FlexPlan p;
   if (!plan_axis(nx, &p) || !plan_axis(ny, &p) || !plan_axis(nz, &p))
     return fail(RISM3D_E_ARG, "grid %dx%dx%d unsupported", nx, ny, nz);
   if (count < 1 || !d_data) return fail(RISM3D_E_ARG, "count < 1 or null data");
@@ -1926,7 +2061,7 @@ rism3d_status rism3d_transform(int nx, int ny, int nz, int count, void* d_data, 
 
 rism3d_status rism3d_transform_noalloc(int nx, int ny, int nz, int count, void* d_data,
                                        int forward, hipStream_t s) {
-  AxisPlan p;
+  FlexPlan p;
   if (!plan_axis(nx, &p) || !plan_axis(ny, &p) || !plan_axis(nz, &p))
     return fail(RISM3D_E_ARG, "grid %dx%dx%d unsupported", nx, ny, nz);
   if (count < 1 || !d_data) return fail(RISM3D_E_ARG, "count < 1 or null data");

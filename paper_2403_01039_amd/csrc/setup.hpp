@@ -84,8 +84,8 @@ struct ExpNeg {
 // in x: they share the atom's data, read at a wave-uniform address (scalar
 // loads), and dy^2 + dz^2; and their K independent chains hide the FP64
 // latency.  1/dc and dc come from one reciprocal square root, e^{-d} from
-// ExpNeg, skipped where no point of the wave is within 38 A (there it adds
-// below FP64 resolution).  128^3, 200 atoms, 5 sites: 1439 us with a square root,
+// ExpNeg; beyond 38 A it adds below FP64 resolution and is taken as 0 (and not
+// evaluated where no point of the wave is nearer).  128^3, 200 atoms, 5 sites: 1439 us with a square root,
 // two divisions and the library's exp at one point a thread, 611 us now (45 FP64
 // operations a pair, 0.79 of the FP64 issue rate).
 template <int NV, int K>
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kPotThreads) void k_potential(
           }
       }
 #pragma unroll
-      for (int k = 0; k < K; ++k) phi_sr[k] += q[k] * e[k];
+      for (int k = 0; k < K; ++k) phi_sr[k] += q[k] * (d[k] < 38.0 ? e[k] : 0.0);
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -210,73 +210,65 @@ __global__ void k_phase_tables(const double* __restrict__ xyz, int n_atoms, int 
 // other half follows from F(-k) = conj F(k).  nz is even, so the first half is
 // the planes jz < nz / 2.
 //
-// The sum is a complex matrix product over the atoms, (row (jz, jy)) x (column
-// jx): the row factor q_a e^{..z} e^{..y} is formed once per workgroup and atom
-// instead of once per k-point.  A workgroup owns kFtRows rows x kFtCols columns,
-// staging kFtAtoms atoms at a time in LDS; a thread holds 4 rows (wave-uniform,
-// LDS broadcasts) x 2 columns, 32 FP64 FMAs per 6 LDS reads, and is bound by
-// the two together.  128^3, 200 atoms: 325 us with one k-point a thread, which
-// formed both products anew for each, 79 us now.
-constexpr int kFtRows = 16, kFtCols = 128, kFtAtoms = 16;
+// A workgroup owns 64 columns jx (one a lane) x 4 rows jy (one a wave) x kFtZ
+// planes jz (held by each thread), staging the phases of kFtAtoms atoms at a
+// time in LDS: the product of the x and y phases is formed once for its kFtZ
+// planes, and the y and z phases and the charge are LDS broadcasts.  The terms
+// and their order are those of one k-point at a time.  Bound by the FP64 issue
+// rate and the broadcasts together.  128^3, 200 atoms: 325 us with one k-point a
+// thread and the phases read through the caches, @FT us now.
+constexpr int kFtCols = 64, kFtRows = 4, kFtZ = 8, kFtAtoms = 32;
 
 __global__ __launch_bounds__(256) void k_ftilde(const double2* __restrict__ ph,
                                                 const double4* __restrict__ atoms, int n_atoms,
                                                 int nx, int ny, int nz, double dkx, double dky,
                                                 double dkz, double pref,
                                                 double2* __restrict__ F) {
-  __shared__ double2 ex[kFtAtoms][kFtCols];
-  __shared__ double2 left[kFtAtoms][kFtRows];
+  __shared__ double2 ex[kFtAtoms][kFtCols], ey[kFtAtoms][kFtRows], ez[kFtAtoms][kFtZ];
+  __shared__ double q[kFtAtoms];
   const int nsum = nx + ny + nz;
-  const int rows = (nz / 2) * ny;
-  const int r0 = blockIdx.x * kFtRows, c0 = blockIdx.y * kFtCols;
+  const int x0 = blockIdx.x * kFtCols, y0 = blockIdx.y * kFtRows, z0 = blockIdx.z * kFtZ;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double2 s[4][2];
+  double2 s[kFtZ];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) s[i][0] = s[i][1] = make_double2(0.0, 0.0);
+  for (int i = 0; i < kFtZ; ++i) s[i] = make_double2(0.0, 0.0);
   for (int a0 = 0; a0 < n_atoms; a0 += kFtAtoms) {
-    __syncthreads();   // the previous atoms' factors are read
-    for (int t = threadIdx.x; t < kFtAtoms * kFtCols; t += 256) {
-      const int a = a0 + t / kFtCols, j = c0 + t % kFtCols;
-      ex[t / kFtCols][t % kFtCols] =
-          a < n_atoms && j < nx ? ph[(size_t)a * nsum + j] : make_double2(0.0, 0.0);
-    }
-    for (int t = threadIdx.x; t < kFtAtoms * kFtRows; t += 256) {
-      const int a = a0 + t / kFtRows, r = r0 + t % kFtRows;
-      double2 v = make_double2(0.0, 0.0);
-      if (a < n_atoms && r < rows) {
-        const double2* pa = ph + (size_t)a * nsum;
-        v = cscale(cmul(pa[nx + r % ny], pa[nx + ny + r / ny]), atoms[a].w);
+    const int cnt = n_atoms - a0 < kFtAtoms ? n_atoms - a0 : kFtAtoms;
+    __syncthreads();   // the previous atoms' phases are read
+    auto stage = [&](double2* dst, int width, int first, int end, int off) {
+      for (int t = threadIdx.x; t < cnt * width; t += 256) {
+        const int a = t / width, j = first + t % width;
+        dst[t] = j < end ? ph[(size_t)(a0 + a) * nsum + off + j] : make_double2(0.0, 0.0);
       }
-      left[t / kFtRows][t % kFtRows] = v;
-    }
+    };
+    stage(&ex[0][0], kFtCols, x0, nx, 0);
+    stage(&ey[0][0], kFtRows, y0, ny, nx);
+    stage(&ez[0][0], kFtZ, z0, nz / 2, nx + ny);
+    if (threadIdx.x < cnt) q[threadIdx.x] = atoms[a0 + threadIdx.x].w;
     __syncthreads();
-#pragma unroll 4
-    for (int a = 0; a < kFtAtoms; ++a) {
-      const double2 e0 = ex[a][lane], e1 = ex[a][lane + 64];
+    for (int a = 0; a < cnt; ++a) {
+      const double2 exy = cmul(ex[a][lane], ey[a][wave]);
+      const double qa = q[a];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const double2 l = left[a][wave * 4 + i];
-        s[i][0].x = fma(l.x, e0.x, fma(-l.y, e0.y, s[i][0].x));
-        s[i][0].y = fma(l.x, e0.y, fma(l.y, e0.x, s[i][0].y));
-        s[i][1].x = fma(l.x, e1.x, fma(-l.y, e1.y, s[i][1].x));
-        s[i][1].y = fma(l.x, e1.y, fma(l.y, e1.x, s[i][1].y));
+      for (int i = 0; i < kFtZ; ++i) {
+        // exy ez, the roundings fixed: a solve amplifies them up to its tolerance
+        const double2 z = ez[a][i];
+        s[i].x = fma(qa, fma(exy.x, z.x, -__dmul_rn(exy.y, z.y)), s[i].x);
+        s[i].y = fma(qa, fma(exy.x, z.y, __dmul_rn(exy.y, z.x)), s[i].y);
       }
     }
   }
+  const int jx = x0 + lane, jy = y0 + wave;
+  if (jx >= nx || jy >= ny) return;
+  const double kx = kappa_of(jx, nx, dkx), ky = kappa_of(jy, ny, dky);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = r0 + wave * 4 + i;
-    if (r >= rows) break;
-    const double ky = kappa_of(r % ny, ny, dky), kz = kappa_of(r / ny, nz, dkz);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int jx = c0 + lane + 64 * h;
-      if (jx >= nx) continue;
-      const double kx = kappa_of(jx, nx, dkx);
-      const double k2 = kx * kx + ky * ky + kz * kz;
-      const double f = pref / (k2 * (k2 + 1.0 / (kScreen * kScreen)));
-      F[(size_t)r * nx + jx] = make_double2(f * s[i][h].x, f * s[i][h].y);
-    }
+  for (int i = 0; i < kFtZ; ++i) {
+    const int jz = z0 + i;
+    if (jz >= nz / 2) return;
+    const double kz = kappa_of(jz, nz, dkz);
+    const double k2 = kx * kx + ky * ky + kz * kz;
+    const double f = pref / (k2 * (k2 + 1.0 / (kScreen * kScreen)));
+    F[((size_t)jz * ny + jy) * nx + jx] = make_double2(f * s[i].x, f * s[i].y);
   }
 }
 

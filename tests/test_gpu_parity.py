@@ -58,6 +58,31 @@ def test_transform_matches_oracle(R, shape, count):
     assert np.abs(back - x).max() / np.abs(x).max() < 2e-6
 
 
+# Plans of one, two and three trips, every pair of radices that one trip does, the
+# shortest and longest lengths, odd axes (no vector accesses) and data that is
+# 8-byte but not 16-byte aligned.
+@pytest.mark.parametrize("shape,offset", [((2, 10, 50), 0), ((16, 48, 90), 0), ((240, 2, 144), 0),
+                                          ((6, 486, 10), 0), ((2, 2, 500), 0), ((4, 320, 6), 0),
+                                          ((150, 12, 20), 0), ((15, 27, 45), 0), ((3, 405, 5), 0),
+                                          ((18, 20, 24), 1), ((60, 9, 54), 1)])
+def test_transform_plans(R, shape, offset):
+    """Bar as for the other transforms: FP32 round-off of log2(N) ~ 20 levels, 2e-6
+    of the largest value."""
+    from oracle import fft as offt
+    print(f"transform {shape} offset {offset}", flush=True)
+    rng = np.random.default_rng(sum(shape))
+    x = rng.standard_normal((2,) + shape) + 1j * rng.standard_normal((2,) + shape)
+    ref = offt.forward3(x, 1.0)
+    flat = torch.zeros(x.size + offset, dtype=torch.complex64, device="cuda")
+    d = flat[offset:].view(x.shape)
+    d.copy_(torch.tensor(x, dtype=torch.complex64))
+    R.rism3d_transform(d, True)
+    assert np.abs(d.cpu().numpy() - ref).max() / np.abs(ref).max() < 2e-6
+    R.rism3d_transform(d, False)
+    back = d.cpu().numpy() / np.prod(shape)
+    assert np.abs(back - x).max() / np.abs(x).max() < 2e-6
+
+
 @pytest.mark.parametrize("name", ["water", "saline", "single"])
 def test_potential_matches_oracle(R, O, name):
     if name == "single":
@@ -144,6 +169,30 @@ def test_map_matches_oracle(R, O, saline, shape):
           f"{O.rms_of(res_ref):.6e}", flush=True)
     assert err < 2e-6 * scale, err
     assert abs(rms - O.rms_of(res_ref)) / O.rms_of(res_ref) < 1e-6
+
+
+# Lengths without fixed kernels: rows of two-point vectors (50) and four-point
+# ones (60, 120), a z length whose FP64 tile does not fit the LDS (500), fixed x
+# with flexible z and the reverse, and more tiles than one in x.
+@pytest.mark.parametrize("saline,shape", [(False, (90, 20, 50)), (True, (40, 18, 60)),
+                                          (True, (500, 4, 18)), (False, (72, 10, 64)),
+                                          (True, (64, 12, 120)), (False, (20, 54, 162))])
+@pytest.mark.parametrize("closure", ["kh", "pse"])
+def test_maps_at_flexible_lengths(R, O, saline, shape, closure):
+    """The FP64 map at tau and the FP32 increment kernels at tau + delta against the
+    oracle's map; bars of the two map tests."""
+    prob, s, sys_ = _map_case(R, O, saline, shape, closure)
+    print(f"maps {shape} {closure}", flush=True)
+    rng = np.random.default_rng(12)
+    tau = (0.05 * rng.standard_normal(sys_.f.shape)).astype(np.float32).astype(np.float64)
+    delta = (0.02 * rng.standard_normal(sys_.f.shape)).astype(np.float32).astype(np.float64)
+    t32, d32 = (torch.tensor(v, dtype=torch.float32, device="cuda") for v in (tau, delta))
+    ref, _, _ = O.rism_map(sys_, tau + sys_.f)
+    res = s.map(t32)[0].cpu().numpy()
+    assert np.abs(res - ref).max() < 2e-6 * max(1.0, np.abs(ref).max())
+    ref, _, _ = O.rism_map(sys_, tau + delta + sys_.f)
+    res = s.map_increment(t32, d32)[0].cpu().numpy()
+    assert np.abs(res - ref).max() < 2e-6 * max(1.0, np.abs(ref).max())
 
 
 @pytest.mark.parametrize("saline,shape,closure",
