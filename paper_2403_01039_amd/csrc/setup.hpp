@@ -216,7 +216,7 @@ __global__ void k_phase_tables(const double* __restrict__ xyz, int n_atoms, int 
 // planes, and the y and z phases and the charge are LDS broadcasts.  The terms
 // and their order are those of one k-point at a time.  Bound by the FP64 issue
 // rate and the broadcasts together.  128^3, 200 atoms: 325 us with one k-point a
-// thread and the phases read through the caches, @FT us now.
+// thread and the phases read through the caches, 79 us now.
 constexpr int kFtCols = 64, kFtRows = 4, kFtZ = 8, kFtAtoms = 32;
 
 __global__ __launch_bounds__(256) void k_ftilde(const double2* __restrict__ ph,

@@ -12,7 +12,7 @@
 // Lane l supplies row/column (l & 15) and the K slice 8 (l >> 4) .. +7 of its
 // operand; it receives D rows 4 (l >> 4) .. +3 of column (l & 15), i.e. four
 // consecutive output channels of one voxel (one 8-byte BF16 store).
-// Weight gradients use the same instruction on LDS-transposed tiles.
+// Weight gradients use the same instruction on tiles transposed through LDS.
 #pragma once
 
 #include "common.hpp"
@@ -26,8 +26,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kConvThreads = 256;   // 4 waves
-constexpr int kWgradChunk = 64;     // voxels per LDS tile of the weight gradient
-constexpr int kWgradMaxTiles = 16;  // 16x16 output tiles per wave
 
 // FP32 -> BF16 with round-to-nearest-even (NaN stays NaN); BF16 -> FP32 exact.
 __device__ __forceinline__ uint16_t f2bf(float f) {
@@ -193,198 +191,190 @@ __global__ __launch_bounds__(kConvThreads) void k_conv3(ConvArgs p) {
   }
 }
 
-// Weight gradient of one tap (blockIdx.y): dW[o][tap][i] += sum_v dy[v][o] x[v + off][i]
-// over the voxel chunks of this workgroup; the tiles go through LDS
-// transposed ([channel][voxel]) so each lane reads 8 consecutive voxels of
-// one channel as one 16-byte operand.  With more than 4 16x16 (o, i) tiles
-// the waves share the tiles round-robin over one chunk at a time (R = 1).
-// With at most 4 tiles (the full-resolution layers) R = 4 chunks are staged
-// together and wave w multiplies every tile over chunk w of them; the four
-// partial sums of a tile are added in chunk order at the end.  Each workgroup stores its sums in its own slab of the FP32
-// partial buffer (every element of the slab, zeros where it saw no voxel),
-// which k_sum_slabs adds up in workgroup order (deterministic).
+// Weight and bias gradients, dW[o][tap][i] = sum_v dy[v][o] x[v + off(tap)][i] and
+// db[o] = sum_v dy[v][o].  A workgroup takes one 16-channel tile of inputs and OT
+// tiles of outputs (blockIdx.y) over a run of 16 x 8 x 4 voxel tiles, and does all
+// 27 taps on each tile it stages: the tiles go through LDS transposed, eight
+// voxels in y to a 16-byte operand.
+//   dy: [o][z][x][8 y];  x with its halo: [i][hz][hx][10 y, padded to 12].
+// One matrix instruction takes 4 voxels in x (lane group g) x 8 in y.  Its dy
+// operand serves the 27 taps; the x row of (dz, dx) holds the operands of the
+// three dy, the outer two as they lie and the middle one shifted by one element.
+// The 27 accumulator tiles and one of the bias (against a column of ones) stay in
+// registers.  OT waves' worth of output tiles share an x tile; the other waves
+// split the K steps, and their sums are added in order at the end.  Each
+// workgroup stores its sums in its own slab (laid out as the layer's parameters),
+// and k_sum_slabs adds the slabs in a fixed order, so the gradient is
+// deterministic.
+//
+// Bound by the LDS reads (196 bytes a lane per 27 instructions) close to the
+// matrix cores, and by staging between them.  Training step at 128^3: 5070 us in
+// all layers with every tap restaging its own transposed chunk (and 250 us for the
+// bias in a kernel of its own), 820 us now, 0.14 of the BF16 peak.
 struct WgradArgs {
   ConvIn in;
   const uint16_t* dy;   // BF16 [N][cout_pad]
-  float* dw;            // FP32 partial slabs [gridDim.x][cout][27][cin_real]
+  float* dw;            // FP32 slabs [gridDim.x][cout * 27 * cin_real + cout]
   int cin_real;         // real input channels (the packed input may carry zero padding)
   int cout, cout_pad;
   int nz, ny, nx;
-  int chunks;           // chunks of kWgradChunk voxels per workgroup
+  int tiles, per;       // voxel tiles, and how many a workgroup takes
 };
 
-// chunks staged together for a layer with `tiles` 16x16 (o, i) tiles
-__host__ __device__ constexpr int wgrad_group(int tiles) { return tiles <= 4 ? 4 : 1; }
-// LDS row pitch (elements) of R chunks: 16-byte aligned rows
-__host__ __device__ constexpr int wgrad_pitch(int R) { return kWgradChunk * R + 8; }
+constexpr int kWgX = 16, kWgY = 8, kWgZ = 4;            // voxel tile
+constexpr int kWgRows = (kWgX + 2) * (kWgZ + 2);        // x rows of a channel
+// dwords of a channel in LDS: 6 a row and a pad that makes the pitch 4 (mod 8),
+// for conflict-free 8-byte reads of 16 channels; of a dy channel, likewise
+constexpr int kWgXPitch = kWgRows * 6 + 4, kWgDyPitch = kWgX * kWgZ * 4 + 4;
+constexpr int wgrad_dwords(int OT) { return 16 * kWgXPitch + 16 * OT * kWgDyPitch; }
 
-// Stage CH voxels x (8 ngroups) channels, read channels last by load(voxel,
-// group), into dst[channel][voxel] (row pitch `pitch` elements, even): each
-// thread takes two neighbouring voxels of one channel group and stores, per
-// channel, their two 2-byte elements as one 4-byte word.
-template <typename Load>
-__device__ __forceinline__ void stage_pairs(uint16_t* dst, int pitch, int CH, int ngroups,
-                                            Load load) {
-  for (int it = threadIdx.x; it < (CH / 2) * ngroups; it += kConvThreads) {
-    const int vp = it / ngroups, cg = it - vp * ngroups;
-    const u32x4 a = __builtin_bit_cast(u32x4, load(2 * vp, cg));
-    const u32x4 b = __builtin_bit_cast(u32x4, load(2 * vp + 1, cg));
+// Stores channels 8 cg .. + 7 of two voxels that follow each other in y as one
+// dword a channel at dst + c * pitch.
+__device__ __forceinline__ void store_pair(uint32_t* dst, int pitch, bf16x8 va, bf16x8 vb) {
+  const u32x4 a = __builtin_bit_cast(u32x4, va), b = __builtin_bit_cast(u32x4, vb);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      uint32_t* row = reinterpret_cast<uint32_t*>(dst + (size_t)(cg * 8 + 2 * e) * pitch + 2 * vp);
-      row[0] = (a[e] & 0xffffu) | (b[e] << 16);                              // channel 2e
-      row[pitch / 2] = (a[e] >> 16) | (b[e] & 0xffff0000u);                  // channel 2e + 1
-    }
+  for (int e = 0; e < 4; ++e) {
+    dst[(2 * e) * pitch] = (a[e] & 0xffffu) | (b[e] << 16);
+    dst[(2 * e + 1) * pitch] = (a[e] >> 16) | (b[e] & 0xffff0000u);
   }
 }
 
-template <int R>
+template <int OT>
 __global__ __launch_bounds__(kConvThreads) void k_conv3_wgrad(WgradArgs p) {
-  extern __shared__ __align__(16) uint16_t smem[];
-  constexpr int PITCH = wgrad_pitch(R);
-  constexpr int CH = kWgradChunk * R;   // voxels staged at once
-  const int cin = p.in.ca + p.in.cb;
-  const int cit = (cin + 15) >> 4;          // input-channel tiles (x tile rows padded to 16)
-  const int cot = p.cout_pad >> 4;
-  const int ntiles = cot * cit;
-  uint16_t* dyT = smem;                             // [cout_pad][PITCH]
-  uint16_t* xT = smem + (size_t)p.cout_pad * PITCH;  // [cit * 16][PITCH]
+  __shared__ __align__(16) uint32_t wsm[wgrad_dwords(OT)];
+  uint32_t* xs = wsm;                      // [16][kWgXPitch]
+  uint32_t* ds = wsm + 16 * kWgXPitch;     // [16 OT][kWgDyPitch]
+  constexpr int WK = 4 / OT;               // waves that share an output tile
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = lane & 15, g = lane >> 4;
-  const int tap = blockIdx.y;
-  int dz, dy, dx;
-  tap_offset(tap, dz, dy, dx);
-  const int N = p.nz * p.ny * p.nx;
-  f32x4 acc[kWgradMaxTiles];
+  const int ot = wave % OT, ks = wave / OT;
+  const int cin = p.in.ca + p.in.cb;
+  const int cit = (cin + 15) >> 4;
+  const int ti = (int)blockIdx.y % cit, o0 = (int)blockIdx.y / cit * OT * 16;
+  const int cgi = (cin - ti * 16) >= 16 ? 2 : 1;   // 8-channel groups of this input tile
+  const int tx = (p.nx + kWgX - 1) / kWgX, ty = (p.ny + kWgY - 1) / kWgY;
+  f32x4 acc[27], accb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int k = 0; k < kWgradMaxTiles; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // zero the padding rows of the x tile once (channels cin .. cit*16)
-  for (int r = cin + (threadIdx.x >> 6); r < cit * 16; r += 4)
-    for (int c = lane; c < PITCH; c += 64) xT[(size_t)r * PITCH + c] = 0;
-  const int cgo = p.cout_pad >> 3, cgi = cin >> 3;
-  const int vend = ((int)blockIdx.x + 1) * p.chunks * kWgradChunk;   // this workgroup's range
-  for (int ch = 0; ch < p.chunks; ch += R) {
-    const int v0 = ((int)blockIdx.x * p.chunks + ch) * kWgradChunk;
-    if (v0 >= N) break;
+  for (int t = 0; t < 27; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const u32x4 one4 = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, one4);
+  const int t_end = min(((int)blockIdx.x + 1) * p.per, p.tiles);
+  for (int t = (int)blockIdx.x * p.per; t < t_end; ++t) {
+    const int x0 = t % tx * kWgX, y0 = t / tx % ty * kWgY, z0 = t / (tx * ty) * kWgZ;
+    __syncthreads();   // the previous tile's operands are read
+    for (int it = threadIdx.x; it < kWgX * kWgZ * (kWgY / 2) * 2 * OT; it += kConvThreads) {
+      const int cg = it % (2 * OT), r = it / (2 * OT);
+      const int xx = r % kWgX, yp = r / kWgX % (kWgY / 2), zz = r / (kWgX * (kWgY / 2));
+      const int x = x0 + xx, y = y0 + 2 * yp, z = z0 + zz, o = o0 + cg * 8;
+      bf16x8 a = zero8(), b = zero8();
+      if (x < p.nx && z < p.nz && o < p.cout_pad) {
+        const uint16_t* q = p.dy + (((size_t)z * p.ny + y) * p.nx + x) * p.cout_pad + o;
+        if (y < p.ny) a = ld8(q);
+        if (y + 1 < p.ny) b = ld8(q + (size_t)p.nx * p.cout_pad);
+      }
+      store_pair(ds + cg * 8 * kWgDyPitch + (zz * kWgX + xx) * 4 + yp, kWgDyPitch, a, b);
+    }
+    for (int it = threadIdx.x; it < kWgRows * (kWgY / 2 + 1) * cgi; it += kConvThreads) {
+      const int cg = it % cgi, r = it / cgi;
+      const int hx = r % (kWgX + 2), q = r / (kWgX + 2);
+      const int yp = q % (kWgY / 2 + 1), hz = q / (kWgY / 2 + 1);
+      const int x = x0 + hx - 1, y = y0 + 2 * yp - 1, z = z0 + hz - 1;
+      const bf16x8 a = load_in(p.in, ti * 2 + cg, z, y, x, p.nz, p.ny, p.nx);
+      const bf16x8 b = load_in(p.in, ti * 2 + cg, z, y + 1, x, p.nz, p.ny, p.nx);
+      store_pair(xs + cg * 8 * kWgXPitch + (hz * (kWgX + 2) + hx) * 6 + yp, kWgXPitch, a, b);
+    }
     __syncthreads();
-    stage_pairs(dyT, PITCH, CH, cgo, [&](int vv, int cg) {
-      const int v = v0 + vv;
-      return v < N && v < vend ? ld8(p.dy + (size_t)v * p.cout_pad + cg * 8) : zero8();
-    });
-    stage_pairs(xT, PITCH, CH, cgi, [&](int vv, int cg) {
-      const int v = v0 + vv;
-      bf16x8 val = zero8();
-      if (v < N && v < vend) {
-        const int x = v % p.nx, y = (v / p.nx) % p.ny, z = v / (p.nx * p.ny);
-        val = load_in(p.in, cg, z + dz, y + dy, x + dx, p.nz, p.ny, p.nx);
-      }
-      return val;
-    });
-    __syncthreads();
-    if constexpr (R == 1) {
+#pragma unroll 1
+    for (int c = ks; c < kWgZ * (kWgX / 4); c += WK) {
+      const int zz = c / (kWgX / 4), xb = c % (kWgX / 4) * 4 + g;
+      const bf16x8 a = __builtin_bit_cast(
+          bf16x8, *reinterpret_cast<const u32x4*>(ds + (ot * 16 + j) * kWgDyPitch +
+                                                  (zz * kWgX + xb) * 4));
+      accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, accb, 0, 0, 0);
 #pragma unroll
-      for (int k = 0; k < kWgradMaxTiles; ++k) {
-        const int t = wave + 4 * k;
-        if (t < ntiles) {
-          const int to = t / cit, ti = t - to * cit;
+      for (int dz = 0; dz < 3; ++dz)
 #pragma unroll
-          for (int kk = 0; kk < kWgradChunk; kk += 32) {
-            const bf16x8 a = ld8(dyT + (size_t)(to * 16 + j) * PITCH + kk + 8 * g);
-            const bf16x8 b = ld8(xT + (size_t)(ti * 16 + j) * PITCH + kk + 8 * g);
-            acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[k], 0, 0, 0);
-          }
+        for (int dx = 0; dx < 3; ++dx) {
+          const uint32_t* row = xs + j * kWgXPitch + ((zz + dz) * (kWgX + 2) + xb + dx) * 6;
+          const u32x2 lo = *reinterpret_cast<const u32x2*>(row);
+          const u32x2 mi = *reinterpret_cast<const u32x2*>(row + 2);
+          const uint32_t hi = row[4];
+          const u32x4 b0 = {lo[0], lo[1], mi[0], mi[1]};
+          const u32x4 b1 = {__builtin_amdgcn_alignbit(lo[1], lo[0], 16),
+                            __builtin_amdgcn_alignbit(mi[0], lo[1], 16),
+                            __builtin_amdgcn_alignbit(mi[1], mi[0], 16),
+                            __builtin_amdgcn_alignbit(hi, mi[1], 16)};
+          const u32x4 b2 = {lo[1], mi[0], mi[1], hi};
+          f32x4* q = acc + dz * 9 + dx;
+          q[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, b0), q[0], 0,
+                                                         0, 0);
+          q[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, b1), q[3], 0,
+                                                         0, 0);
+          q[6] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, b2), q[6], 0,
+                                                         0, 0);
         }
-      }
-    } else {
-      // ntiles <= 4: wave w takes every tile over chunk w
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (k < ntiles) {
-          const int to = k / cit, ti = k - to * cit;
-#pragma unroll
-          for (int kk = 0; kk < kWgradChunk; kk += 32) {
-            const int k0 = wave * kWgradChunk + kk + 8 * g;
-            const bf16x8 a = ld8(dyT + (size_t)(to * 16 + j) * PITCH + k0);
-            const bf16x8 b = ld8(xT + (size_t)(ti * 16 + j) * PITCH + k0);
-            acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[k], 0, 0, 0);
-          }
-        }
-      }
     }
   }
-  float* slab = p.dw + (size_t)blockIdx.x * p.cout * 27 * p.cin_real;
-  auto store_tile = [&](int t, const f32x4& r) {
-    const int to = t / cit, ti = t - to * cit;
-    const int i = ti * 16 + j;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int o = to * 16 + 4 * g + e;
-      if (o < p.cout && i < p.cin_real) slab[((size_t)o * 27 + tap) * p.cin_real + i] = r[e];
-    }
-  };
-  if constexpr (R == 1) {
-#pragma unroll
-    for (int k = 0; k < kWgradMaxTiles; ++k) {
-      const int t = wave + 4 * k;
-      if (t < ntiles) store_tile(t, acc[k]);
-    }
-  } else {
-    // the four partial sums of each tile, added in chunk order: wave t < ntiles
-    // stores tile t
-    __syncthreads();   // the last chunk's tiles are read; smem is reused
-    f32x4* part = reinterpret_cast<f32x4*>(smem);   // [wave][tile][lane]
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (k < ntiles) part[(wave * 4 + k) * 64 + lane] = acc[k];
+  // the K splits of an output tile, added in order
+  f32x4* part = reinterpret_cast<f32x4*>(wsm);   // [OT][28][64]
+  static_assert(wgrad_dwords(OT) >= OT * 28 * 64 * 4, "scratch of the sums");
+#pragma unroll 1
+  for (int k = 1; k < WK; ++k) {
     __syncthreads();
-    if (wave < ntiles) {
-      f32x4 r = part[wave * 64 + lane];
-      for (int q = 1; q < 4; ++q) r += part[(q * 4 + wave) * 64 + lane];
-      store_tile(wave, r);
+    if (ks == k) {
+#pragma unroll
+      for (int t = 0; t < 27; ++t) part[(ot * 28 + t) * 64 + lane] = acc[t];
+      part[(ot * 28 + 27) * 64 + lane] = accb;
     }
+    __syncthreads();
+    if (ks == 0) {
+#pragma unroll
+      for (int t = 0; t < 27; ++t) acc[t] += part[(ot * 28 + t) * 64 + lane];
+      accb += part[(ot * 28 + 27) * 64 + lane];
+    }
+  }
+  if (ks != 0) return;
+  const size_t nw = (size_t)p.cout * 27 * p.cin_real;
+  float* slab = p.dw + (size_t)blockIdx.x * (nw + p.cout);
+  const int i = ti * 16 + j;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int o = o0 + ot * 16 + 4 * g + e;
+    if (o >= p.cout) continue;
+    if (i < p.cin_real) {
+#pragma unroll
+      for (int t = 0; t < 27; ++t) slab[((size_t)o * 27 + t) * p.cin_real + i] = acc[t][e];
+    }
+    if (ti == 0 && j == 0) slab[nw + o] = accb[e];
   }
 }
 
-// Partial bias gradients: slab b (this workgroup) of part receives
-// sum_v dy[v][o] over the workgroup's voxels (BF16 dy, FP32 sums), the lanes
-// of one channel added in lane order; k_sum_slabs adds the slabs up.
-__global__ __launch_bounds__(kConvThreads) void k_bias_grad(const uint16_t* __restrict__ dy,
-                                                            int N, int cout, int cout_pad,
-                                                            float* __restrict__ part) {
-  __shared__ float red[kConvThreads];
-  const int c = threadIdx.x % cout_pad;
-  const int lanes_per_voxel = kConvThreads / cout_pad;   // cout_pad divides 256
-  const int sub = threadIdx.x / cout_pad;
-  float s = 0.0f;
-  for (int v = (int)blockIdx.x * lanes_per_voxel + sub; v < N; v += (int)gridDim.x * lanes_per_voxel)
-    s += bf2f(dy[(size_t)v * cout_pad + c]);
-  red[threadIdx.x] = s;
-  __syncthreads();
-  if ((int)threadIdx.x < cout) {
-    float t = 0.0f;
-    for (int k = 0; k < lanes_per_voxel; ++k) t += red[k * cout_pad + threadIdx.x];
-    part[(size_t)blockIdx.x * cout + threadIdx.x] = t;
-  }
-}
-
-// dst[e] += sum_b part[b][e] over the n_slab slabs of n elements, in slab
-// order (the fixed-order end of the weight and bias gradients).
-__global__ void k_sum_slabs(const float* __restrict__ part, int n_slab, size_t n,
-                            float* __restrict__ dst) {
-  const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  // 16 slabs' loads in flight at a time; the additions keep slab order
+// dst[e] = sum_b part[b][e] over the n_slab slabs of n elements.  Thread row r of
+// blockDim.y adds slabs r, r + blockDim.y, ... in order, and the rows are added in
+// order (a fixed order: the gradients are deterministic).
+__global__ __launch_bounds__(1024) void k_sum_slabs(const float* __restrict__ part, int n_slab,
+                                                    size_t n, float* __restrict__ dst) {
+  __shared__ float red[16][64];
+  const size_t e = (size_t)blockIdx.x * 64 + threadIdx.x;
   float t = 0.0f;
-  int b = 0;
-  for (; b + 16 <= n_slab; b += 16) {
-    float v[16];
+  if (e < n) {
+    int b = threadIdx.y;
+    const int Y = blockDim.y;
+    for (; b + 7 * Y < n_slab; b += 8 * Y) {   // 8 loads in flight
+      float v[8];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = part[(size_t)(b + k) * n + e];
+      for (int k = 0; k < 8; ++k) v[k] = part[(size_t)(b + k * Y) * n + e];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) t += v[k];
+      for (int k = 0; k < 8; ++k) t += v[k];
+    }
+    for (; b < n_slab; b += Y) t += part[(size_t)b * n + e];
   }
-  for (; b < n_slab; ++b) t += part[(size_t)b * n + e];
-  dst[e] += t;
+  red[threadIdx.y][threadIdx.x] = t;
+  __syncthreads();
+  if (threadIdx.y == 0 && e < n) {
+    for (int r = 1; r < (int)blockDim.y; ++r) t += red[r][threadIdx.x];
+    dst[e] = t;
+  }
 }
 
 // Average over 2x2x2 blocks (BF16 in and out, FP32 sums); one thread per
@@ -573,11 +563,6 @@ __global__ void k_adam(float* __restrict__ theta, float* __restrict__ m, float* 
   m[id] = mm;
   v[id] = vv;
   theta[id] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
-}
-
-__global__ void k_fill_f32(float* __restrict__ p, size_t n, float value) {
-  const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id < n) p[id] = value;
 }
 
 }  // namespace net

@@ -39,29 +39,30 @@ struct NetPlan {
 
 constexpr int kMsePartials = 1024;
 
-// Workgroups per tap of the weight gradient over N voxels (chunks of
-// kWgradChunk voxels, about 96 workgroups x 27 taps at full size), and the
-// voxel chunks each one takes.
-size_t wgrad_per(size_t N) {
-  const size_t chunks_total = (N + net::kWgradChunk - 1) / net::kWgradChunk;
-  const size_t wg_target = 96;
-  return std::max<size_t>(1, (chunks_total + wg_target - 1) / wg_target);
-}
-size_t wgrad_blocks(size_t N) {
-  const size_t chunks_total = (N + net::kWgradChunk - 1) / net::kWgradChunk;
-  return (chunks_total + wgrad_per(N) - 1) / wgrad_per(N);
-}
-size_t bias_blocks(size_t N, int cout_pad) {
-  const size_t per_block = (size_t)(net::kConvThreads / cout_pad);
-  return std::min<size_t>(1024, (N + per_block - 1) / per_block);
+// The weight-gradient launch of a layer: output tiles a workgroup holds (two share
+// a staged input tile; four would leave one workgroup a compute unit), voxel
+// tiles, and the workgroups (= slabs) they are dealt to, for about 512 workgroups
+// (two a compute unit) in all.
+struct WgradShape {
+  int ot, ypairs, tiles, per, slabs;
+};
+WgradShape wgrad_shape(int cin_pad, int cout_pad, int nx, int ny, int nz) {
+  WgradShape w;
+  const int cot = cout_pad / 16, cit = (cin_pad + 15) / 16;
+  w.ot = cot >= 2 ? 2 : 1;
+  w.ypairs = cit * ((cot + w.ot - 1) / w.ot);
+  w.tiles = ((nx + net::kWgX - 1) / net::kWgX) * ((ny + net::kWgY - 1) / net::kWgY) *
+            ((nz + net::kWgZ - 1) / net::kWgZ);
+  const int want = std::max(1, 512 / w.ypairs);
+  w.per = std::max(1, (w.tiles + want - 1) / want);
+  w.slabs = (w.tiles + w.per - 1) / w.per;
+  return w;
 }
 
 rism3d_status net_plan(const rism3d_unet_config* cfg, int nx, int ny, int nz, NetPlan* P) {
   if (!cfg) return fail(RISM3D_E_ARG, "null network configuration");
   const int L = cfg->levels;
   if (L < 1 || L > kNetMaxLevels) return fail(RISM3D_E_ARG, "levels must be in 1..%d", kNetMaxLevels);
-  // (the weight-gradient kernel holds at most 64 16x16 tiles per workgroup:
-  // 128 x 128 and 192 x 64 channel pairs at base 16, 4 levels)
   if (cfg->base < 16 || cfg->base % 16 || (cfg->base << (L - 1)) > 128)
     return fail(RISM3D_E_ARG, "base channels must be a multiple of 16 with base * 2^(levels-1) <= 128");
   if (cfg->in_channels < 1 || cfg->in_channels > 64 || cfg->out_channels < 1 ||
@@ -105,8 +106,9 @@ rism3d_status net_plan(const rism3d_unet_config* cfg, int nx, int ny, int nz, Ne
     add(P->c(l), P->c(l), l);
   }
   add(P->c(0), cfg->out_channels, 0);
+  // (192 x 128 channel pairs at most: base 16, 4 levels)
   for (const NetLayer& ly : P->layers)
-    if ((ly.cout_pad / 16) * ((ly.cin_pad + 15) / 16) > 4 * net::kWgradMaxTiles)
+    if ((ly.cout_pad / 16) * ((ly.cin_pad + 15) / 16) > 64)
       return fail(RISM3D_E_ARG, "layer %d x %d channels exceeds the weight-gradient tile budget",
                   ly.cin, ly.cout);
 
@@ -147,11 +149,12 @@ rism3d_status net_plan(const rism3d_unet_config* cfg, int nx, int ny, int nz, Ne
   P->dyp = take(max_cout_pad * 2);
   P->partials = take(kMsePartials * sizeof(double));
   P->loss = take(sizeof(double));
-  size_t slab_floats = 0;   // partial slabs of the largest weight (or bias) gradient
+  size_t slab_floats = 0;   // the slabs of the largest layer's gradient
   for (const NetLayer& ly : P->layers) {
-    const size_t w = wgrad_blocks(P->nvox[ly.level]) * (size_t)ly.cout * 27 * ly.cin;
-    const size_t b = bias_blocks(P->nvox[ly.level], ly.cout_pad) * (size_t)ly.cout;
-    slab_floats = std::max(slab_floats, std::max(w, b));
+    const WgradShape w = wgrad_shape(ly.cin_pad, ly.cout_pad, P->nx[ly.level], P->ny[ly.level],
+                                     P->nz[ly.level]);
+    slab_floats = std::max(slab_floats,
+                           (size_t)w.slabs * ((size_t)ly.cout * 27 * ly.cin + ly.cout));
   }
   P->slabs = take(slab_floats * sizeof(float));
   P->total_train = off;
@@ -305,11 +308,11 @@ void net_conv_dx(const NetPlan& P, const NetLayer& ly, void* ws, const uint16_t*
   net_conv<net::EPI_F32_CL>(a, s);
 }
 
+// Weight and bias gradients of one layer, written to grad + w_off (b follows W).
 void net_conv_dw(const NetPlan& P, const NetLayer& ly, const net::ConvIn& in, void* ws,
                  const uint16_t* dyp, float* grad, hipStream_t s) {
-  const size_t N = P.nvox[ly.level];
-  const size_t per = wgrad_per(N);
-  const size_t nbx = wgrad_blocks(N);
+  const WgradShape sh = wgrad_shape(ly.cin_pad, ly.cout_pad, P.nx[ly.level], P.ny[ly.level],
+                                    P.nz[ly.level]);
   float* slabs = wsp<float>(ws, P.slabs);
   net::WgradArgs w;
   w.in = in;
@@ -321,21 +324,17 @@ void net_conv_dw(const NetPlan& P, const NetLayer& ly, const net::ConvIn& in, vo
   w.nz = P.nz[ly.level];
   w.ny = P.ny[ly.level];
   w.nx = P.nx[ly.level];
-  w.chunks = (int)per;
-  const int cit = (ly.cin_pad + 15) / 16;
-  const int R = net::wgrad_group((ly.cout_pad / 16) * cit);
-  const size_t lds = ((size_t)ly.cout_pad + (size_t)cit * 16) * net::wgrad_pitch(R) * 2;
-  const dim3 grid((unsigned)nbx, 27), block(net::kConvThreads);
-  if (R == 4) hipLaunchKernelGGL(net::k_conv3_wgrad<4>, grid, block, lds, s, w);
-  else hipLaunchKernelGGL(net::k_conv3_wgrad<1>, grid, block, lds, s, w);
-  const size_t nw = (size_t)ly.cout * 27 * ly.cin;
-  hipLaunchKernelGGL(net::k_sum_slabs, dim3(net_blocks(nw, 256)), dim3(256), 0, s, slabs,
-                     (int)nbx, nw, grad + ly.w_off);
-  const unsigned nb = (unsigned)bias_blocks(N, ly.cout_pad);
-  hipLaunchKernelGGL(net::k_bias_grad, dim3(nb), dim3(net::kConvThreads), 0, s, dyp, (int)N,
-                     ly.cout, ly.cout_pad, slabs);
-  hipLaunchKernelGGL(net::k_sum_slabs, dim3(net_blocks(ly.cout, 256)), dim3(256), 0, s, slabs,
-                     (int)nb, (size_t)ly.cout, grad + ly.b_off);
+  w.tiles = sh.tiles;
+  w.per = sh.per;
+  const dim3 grid((unsigned)sh.slabs, (unsigned)sh.ypairs), block(net::kConvThreads);
+  hipLaunchKernelGGL(sh.ot == 2 ? &net::k_conv3_wgrad<2> : &net::k_conv3_wgrad<1>, grid, block, 0,
+                     s, w);
+  const size_t n = (size_t)ly.cout * 27 * ly.cin + ly.cout;
+  // sixteen threads an element where there are slabs for them: 15.5 us a layer of
+  // the 128^3 step with one, 6.0 with up to sixteen
+  const unsigned rows = sh.slabs >= 64 ? 16 : sh.slabs >= 16 ? 4 : 1;
+  hipLaunchKernelGGL(net::k_sum_slabs, dim3(net_blocks(n, 64)), dim3(64, rows), 0, s, slabs,
+                     sh.slabs, n, grad + ly.w_off);
 }
 
 void net_leaky_bwd(const NetPlan& P, size_t y_off, const float* g, int level, int C, void* ws,
@@ -352,8 +351,6 @@ void net_gradient(const NetPlan& P, const float* params, const float* input, con
   const int L = P.cfg.levels;
   float* out = wsp<float>(ws, P.out);
   net_forward(P, params, input, out, ws, s);
-  hipLaunchKernelGGL(net::k_fill_f32, dim3(net_blocks(P.n_params, 256)), dim3(256), 0, s, grad,
-                     P.n_params, 0.0f);
   const NetLayer& lo = P.layers.back();
   hipLaunchKernelGGL(net::k_mse, dim3(kMsePartials), dim3(256), 0, s, out, target, lo.cout,
                      lo.cout_pad, P.nvox[0], wsp<uint16_t>(ws, P.dyp), wsp<double>(ws, P.partials));

@@ -171,6 +171,51 @@ def test_gradient_matches_oracle_with_bf16_rounding(R, monkeypatch):
         off += nw + co
 
 
+# Ragged voxel tiles in every axis, grids below one tile, one and two output
+# tiles a workgroup, and (one level, 576 voxel tiles) two voxel tiles a workgroup.
+@pytest.mark.parametrize("levels,shape", [(3, (8, 24, 40)), (3, (4, 12, 20)), (2, (16, 16, 16)),
+                                          (1, (72, 64, 64))])
+def test_gradient_on_ragged_tiles(R, monkeypatch, levels, shape):
+    """A network whose convolutions add three inputs with weights +-1, on small
+    integers with slope 1/4: every FP32 sum up to a BF16 rounding is then exact,
+    so the rounded values are those of the oracle with the same roundings, and
+    the gradients differ by the FP32 sum over the N voxels alone, 2^-24 of its
+    partial sums (about sqrt(N) terms large): 1e-4 of the layer's largest."""
+    from oracle import unet as U
+    print(f"unet gradient levels={levels} {shape}", flush=True)
+    cfg = R.unet_config(3, 3, levels=levels, base=16, slope=0.25)
+    ocfg = U.Config(levels=levels, base=16, in_channels=3, out_channels=3, slope=0.25)
+    rng = np.random.default_rng(61)
+    parts = []
+    for _, ci, co in ocfg.layers():
+        w = np.zeros((co, 27 * ci))
+        for o in range(co):
+            w[o, rng.choice(27 * ci, 3, replace=False)] = rng.choice([-1.0, 1.0], 3)
+        parts += [w.ravel(), rng.integers(-1, 2, co)]
+    theta = np.concatenate(parts).astype(np.float32)
+    x = rng.integers(-2, 3, shape + (3,)).astype(np.float32)
+    target = rng.integers(-3, 4, shape + (3,)).astype(np.float64)
+    params = torch.tensor(theta, device="cuda")
+    grad = torch.empty_like(params)
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    ws = R.alloc_workspace(R.unet_workspace_bytes(cfg, shape, True))
+    R.unet_gradient(cfg, params, _site_major(x), _site_major(target), grad, ws, loss)
+    leaky, pool2, mse, leaky_bwd = U.leaky, U.pool2, U.mse, U.leaky_backward
+    r = lambda a: bf16_round(a).astype(np.float64)
+    monkeypatch.setattr(U, "leaky", lambda v, sl: r(leaky(v, sl)))
+    monkeypatch.setattr(U, "pool2", lambda v: r(pool2(v)))
+    monkeypatch.setattr(U, "mse", lambda o, t: (mse(o, t)[0], r(mse(o, t)[1])))
+    monkeypatch.setattr(U, "leaky_backward", lambda y, d, sl: r(leaky_bwd(y, d, sl)))
+    ref_loss, ref = U.loss_and_grad(ocfg, theta.astype(np.float64), x.astype(np.float64), target)
+    assert abs(loss.item() - ref_loss) <= 1e-12 * ref_loss
+    g, off = grad.cpu().numpy(), 0
+    for name, ci, co in ocfg.layers():
+        for part, n in (("W", co * 27 * ci), ("b", co)):
+            got, want = g[off:off + n], ref[off:off + n]
+            assert np.abs(got - want).max() <= 1e-4 * np.abs(want).max(), (name, part)
+            off += n
+
+
 def test_gradient_is_bitwise_reproducible(R):
     """The weight and bias gradients are summed over workgroups in a fixed
     order (per-workgroup slabs, then a slab sum), so two evaluations agree
