@@ -77,19 +77,35 @@ __device__ __forceinline__ bf16x8 load_in(const ConvIn& in, int cg, int z, int y
 enum ConvEpilogue {
   EPI_BF16_LEAKY = 0,   // + bias, leaky, BF16 channels last [N][cout_pad]
   EPI_F32_SITE = 1,     // + bias, FP32 site-major [cout][N] (channels < cout)
-  EPI_F32_CL = 2,       // raw FP32 channels last [N][cout_pad]
+  EPI_BF16_DLEAKY = 2,  // times leaky'(.) of the activation act, BF16 channels last [N][cout]
+  EPI_F32_SPLIT = 3,    // raw FP32 channels last: [0, split) to yf, the others to yf2
 };
 
 struct ConvArgs {
   ConvIn in;
   const uint16_t* w;    // packed [cout_pad][27][cin], cin = ca + cb
   const float* bias;    // [cout] (EPI 0, 1)
-  uint16_t* yb;         // EPI_BF16_LEAKY output
-  float* yf;            // EPI_F32_SITE / EPI_F32_CL output
+  uint16_t* yb;         // EPI_BF16_LEAKY / EPI_BF16_DLEAKY output
+  float* yf;            // EPI_F32_SITE / EPI_F32_SPLIT output
+  float* yf2;           // EPI_F32_SPLIT: the skip channels
+  const uint16_t* act;  // EPI_BF16_DLEAKY: the activation, BF16 channels last [N][cout]
+  int split;            // EPI_F32_SPLIT: channels of yf (a multiple of 4)
   int cout, cout_pad;
   int nz, ny, nx;
   float slope;
 };
+
+// d * leaky'(.) of four channels as BF16, the derivative read from the sign of the
+// BF16 activation y.
+__device__ __forceinline__ u32x2 leaky_bwd4(u32x2 y, f32x4 d, float slope) {
+  uint16_t h[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint16_t a = (uint16_t)(e & 1 ? y[e >> 1] >> 16 : y[e >> 1] & 0xffffu);
+    h[e] = f2bf(bf2f(a) > 0.0f ? d[e] : slope * d[e]);
+  }
+  return u32x2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
+}
 
 // Epilogue of one accumulator tile: output channels c0 .. c0 + 3 of voxel v.
 template <int EPI>
@@ -110,8 +126,13 @@ __device__ __forceinline__ void conv_store(const ConvArgs& p, int N, size_t v, i
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (c0 + e < p.cout) p.yf[(size_t)(c0 + e) * N + v] = r[e] + p.bias[c0 + e];
+  } else if (EPI == EPI_BF16_DLEAKY) {
+    const u32x2 y = *reinterpret_cast<const u32x2*>(p.act + v * p.cout + c0);
+    *reinterpret_cast<u32x2*>(p.yb + v * p.cout + c0) = leaky_bwd4(y, r, p.slope);
   } else {
-    *reinterpret_cast<f32x4*>(p.yf + v * p.cout_pad + c0) = r;
+    float* o = c0 < p.split ? p.yf + v * p.split + c0
+                            : p.yf2 + v * (p.cout - p.split) + (c0 - p.split);
+    *reinterpret_cast<f32x4*>(o) = r;
   }
 }
 
@@ -405,69 +426,66 @@ __global__ void k_pool2(const uint16_t* __restrict__ in, uint16_t* __restrict__ 
   *reinterpret_cast<u32x4*>(out + cv * C + g * 8) = o;
 }
 
-// fine[v][c] += coarse[v / 2][c] / 8 (adjoint of the 2x2x2 average), FP32.
-__global__ void k_pool2_bwd_add(const float* __restrict__ coarse, float* __restrict__ fine, int nz,
-                                int ny, int nx, int C) {
+// The gradient at a pooled encoder output, (skip + coarse[v / 2] / 8) leaky'(y) in
+// BF16: the skip branch's FP32 part, the adjoint of the 2x2x2 average, and the
+// activation's derivative in one pass.  Four channels a thread.
+__global__ void k_pool2_bwd_leaky(const float* __restrict__ coarse, const float* __restrict__ skip,
+                                  const uint16_t* __restrict__ y, uint16_t* __restrict__ out,
+                                  int nz, int ny, int nx, int C, float slope) {
   const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t n = (size_t)nz * ny * nx * C;
-  if (id >= n) return;
-  const int c = (int)(id % C);
-  const size_t v = id / C;
-  const int x = (int)(v % nx), y = (int)((v / nx) % ny), z = (int)(v / ((size_t)nx * ny));
-  const size_t cv = ((size_t)(z >> 1) * (ny >> 1) + (y >> 1)) * (nx >> 1) + (x >> 1);
-  fine[id] += 0.125f * coarse[cv * C + c];
+  const int c4 = C >> 2;
+  if (id >= (size_t)nz * ny * nx * c4) return;
+  const unsigned v = (unsigned)(id / c4), row = v / nx, z = row / ny;
+  const unsigned x = v - row * nx, yy = row - z * ny;
+  const size_t cv = ((size_t)(z >> 1) * (ny >> 1) + (yy >> 1)) * (nx >> 1) + (x >> 1);
+  const f32x4 s = reinterpret_cast<const f32x4*>(skip)[id];
+  const f32x4 c = reinterpret_cast<const f32x4*>(coarse)[cv * c4 + (id - (size_t)v * c4)];
+  reinterpret_cast<u32x2*>(out)[id] =
+      leaky_bwd4(reinterpret_cast<const u32x2*>(y)[id], s + 0.125f * c, slope);
 }
 
-// coarse[u][c] = sum of the 8 fine voxels of block u of dx[v][c] (c < ca), the
-// adjoint of nearest-neighbour upsampling; dx has cin channels per voxel.
-__global__ void k_up2_bwd(const float* __restrict__ dx, int cin, int ca, float* __restrict__ coarse,
-                          int nz, int ny, int nx) {
-  const int hz = nz >> 1, hy = ny >> 1, hx = nx >> 1;
+// The gradient at an upsampled tensor, the sum of the eight fine voxels of block u
+// of dx (C channels) times leaky'(y), in BF16.  Four channels a thread.
+__global__ void k_up2_bwd_leaky(const float* __restrict__ dx, const uint16_t* __restrict__ y,
+                                uint16_t* __restrict__ out, int nz, int ny, int nx, int C,
+                                float slope) {
+  const int hz = nz >> 1, hy = ny >> 1, hx = nx >> 1, c4 = C >> 2;
   const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= (size_t)hz * hy * hx * ca) return;
-  const int c = (int)(id % ca);
-  const size_t cv = id / ca;
-  const int x = (int)(cv % hx), y = (int)((cv / hx) % hy), z = (int)(cv / ((size_t)hx * hy));
-  float s = 0.0f;
+  if (id >= (size_t)hz * hy * hx * c4) return;
+  const unsigned cv = (unsigned)(id / c4), row = cv / hx, z = row / hy;
+  const unsigned x = cv - row * hx, yy = row - z * hy;
+  const int g = (int)(id - (size_t)cv * c4);
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
   for (int d = 0; d < 8; ++d) {
-    const size_t v = ((size_t)(2 * z + (d >> 2)) * ny + 2 * y + ((d >> 1) & 1)) * nx + 2 * x + (d & 1);
-    s += dx[v * cin + c];
+    const size_t v = ((size_t)(2 * z + (d >> 2)) * ny + 2 * yy + ((d >> 1) & 1)) * nx + 2 * x + (d & 1);
+    s += reinterpret_cast<const f32x4*>(dx)[v * c4 + g];
   }
-  coarse[id] = s;
+  reinterpret_cast<u32x2*>(out)[id] = leaky_bwd4(reinterpret_cast<const u32x2*>(y)[id], s, slope);
 }
 
-// skip[v][c] = dx[v][ca + c] (the skip-branch part of a concatenated input gradient).
-__global__ void k_take_skip(const float* __restrict__ dx, int cin, int ca, float* __restrict__ skip,
-                            size_t N) {
-  const int cb = cin - ca;
-  const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= N * cb) return;
-  const size_t v = id / cb;
-  skip[id] = dx[v * cin + ca + (id - v * cb)];
-}
-
-// dy_pre = dy * leaky'(.), the derivative read from the sign of the BF16
-// activation output y; BF16 result.
-__global__ void k_leaky_bwd(const uint16_t* __restrict__ y, const float* __restrict__ dy,
-                            uint16_t* __restrict__ out, size_t n, float slope) {
-  const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= n) return;
-  const float d = dy[id];
-  out[id] = f2bf(bf2f(y[id]) > 0.0f ? d : slope * d);
-}
-
-// Site-major FP32 [C][N] -> BF16 channels last [N][cpad] (zero padding).
+// Site-major FP32 [C][N] -> BF16 channels last [N][cpad] (zero padding), one voxel
+// a thread.
 __global__ void k_to_channels_last(const float* __restrict__ in, int C, int cpad, size_t N,
                                    uint16_t* __restrict__ out) {
-  const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= N * cpad) return;
-  const size_t v = id / cpad;
-  const int c = (int)(id - v * cpad);
-  out[id] = c < C ? f2bf(in[(size_t)c * N + v]) : (uint16_t)0;
+  const size_t v = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= N) return;
+  for (int c0 = 0; c0 < cpad; c0 += 8) {
+    u32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int c = c0 + 2 * e;
+      const uint32_t a = c < C ? f2bf(in[(size_t)c * N + v]) : 0u;
+      const uint32_t b = c + 1 < C ? f2bf(in[(size_t)(c + 1) * N + v]) : 0u;
+      o[e] = a | (b << 16);
+    }
+    *reinterpret_cast<u32x4*>(out + v * cpad + c0) = o;
+  }
 }
 
 // Mean squared error over C x N values: per-block FP64 partial sums and the
-// BF16 gradient 2 (o - t) / (C N) channels last [N][cpad] (zero padding).
+// BF16 gradient 2 (o - t) / (C N) channels last [N][cpad] (zero padding), one
+// voxel a thread and step.
 __global__ __launch_bounds__(256) void k_mse(const float* __restrict__ out,
                                              const float* __restrict__ target, int C, int cpad,
                                              size_t N, uint16_t* __restrict__ grad,
@@ -475,17 +493,21 @@ __global__ __launch_bounds__(256) void k_mse(const float* __restrict__ out,
   __shared__ double red[4];
   const double scale = 2.0 / ((double)C * (double)N);
   double s = 0.0;
-  for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < N * cpad;
-       id += (size_t)gridDim.x * blockDim.x) {
-    const size_t v = id / cpad;
-    const int c = (int)(id - v * cpad);
-    float gval = 0.0f;
-    if (c < C) {
-      const double d = (double)out[(size_t)c * N + v] - (double)target[(size_t)c * N + v];
-      s += d * d;
-      gval = (float)(scale * d);
+  for (size_t v = (size_t)blockIdx.x * blockDim.x + threadIdx.x; v < N;
+       v += (size_t)gridDim.x * blockDim.x) {
+    for (int c0 = 0; c0 < cpad; c0 += 8) {
+      u32x4 o = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (c0 + e < C) {
+          const size_t i = (size_t)(c0 + e) * N + v;
+          const double d = (double)out[i] - (double)target[i];
+          s += d * d;
+          o[e >> 1] |= (uint32_t)f2bf((float)(scale * d)) << (16 * (e & 1));
+        }
+      }
+      *reinterpret_cast<u32x4*>(grad + v * cpad + c0) = o;
     }
-    grad[id] = f2bf(gval);
   }
   for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
@@ -493,34 +515,50 @@ __global__ __launch_bounds__(256) void k_mse(const float* __restrict__ out,
   if (threadIdx.x == 0) partials[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-__global__ void k_sum_partials(const double* __restrict__ partials, int n, double scale,
-                               double* __restrict__ out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// *out = scale * the sum of n partials, by one workgroup in a fixed order.
+__global__ __launch_bounds__(256) void k_sum_partials(const double* __restrict__ partials, int n,
+                                                      double scale, double* __restrict__ out) {
+  __shared__ double red[4];
   double s = 0.0;
-  for (int i = 0; i < n; ++i) s += partials[i];
-  *out = s * scale;
+  for (int i = threadIdx.x; i < n; i += 256) s += partials[i];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) *out = scale * (red[0] + red[1] + red[2] + red[3]);
 }
 
 // FP32 master weights W[cout][27][cin] -> BF16 packed [cout_pad][27][cin_pad]
 // (forward) and flipped [cin_pad16][27][cout_pad] with tap k -> 26 - k
-// (backward data: the transposed convolution is a convolution with these).
-__global__ void k_pack_weights(const float* __restrict__ W, int cout, int cin, int cout_pad,
-                               int cin_pad, int cin_pad16, uint16_t* __restrict__ wp,
-                               uint16_t* __restrict__ wf) {
-  const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t nfwd = (size_t)cout_pad * 27 * cin_pad;
-  const size_t nflip = wf ? (size_t)cin_pad16 * 27 * cout_pad : 0;
-  if (id < nfwd) {
-    const int i = (int)(id % cin_pad);
-    const int k = (int)((id / cin_pad) % 27);
-    const int o = (int)(id / ((size_t)cin_pad * 27));
-    wp[id] = (o < cout && i < cin) ? f2bf(W[((size_t)o * 27 + k) * cin + i]) : (uint16_t)0;
-  } else if (id < nfwd + nflip) {
-    const size_t f = id - nfwd;
-    const int o = (int)(f % cout_pad);
-    const int k = (int)((f / cout_pad) % 27);
-    const int i = (int)(f / ((size_t)cout_pad * 27));
-    wf[f] = (o < cout && i < cin) ? f2bf(W[((size_t)o * 27 + (26 - k)) * cin + i]) : (uint16_t)0;
+// (backward data: the transposed convolution is a convolution with these), every
+// layer in one launch (blockIdx.y).
+constexpr int kNetMaxLayers = 23;   // six levels: 12 + 10 + 1
+struct PackLayer {
+  const float* w;
+  uint16_t *wp, *wf;   // wf null: forward only
+  int cout, cin, cout_pad, cin_pad, cin_pad16;
+};
+struct PackTable {
+  PackLayer l[kNetMaxLayers];
+};
+__global__ void k_pack_weights(PackTable t) {
+  const PackLayer& p = t.l[blockIdx.y];
+  const unsigned nfwd = (unsigned)p.cout_pad * 27 * p.cin_pad;
+  const unsigned nflip = p.wf ? (unsigned)p.cin_pad16 * 27 * p.cout_pad : 0;
+  for (unsigned id = blockIdx.x * blockDim.x + threadIdx.x; id < nfwd + nflip;
+       id += gridDim.x * blockDim.x) {
+    if (id < nfwd) {
+      const int i = (int)(id % p.cin_pad);
+      const int k = (int)((id / p.cin_pad) % 27);
+      const int o = (int)(id / ((unsigned)p.cin_pad * 27));
+      p.wp[id] = (o < p.cout && i < p.cin) ? f2bf(p.w[((size_t)o * 27 + k) * p.cin + i]) : (uint16_t)0;
+    } else {
+      const unsigned f = id - nfwd;
+      const int o = (int)(f % p.cout_pad);
+      const int k = (int)((f / p.cout_pad) % 27);
+      const int i = (int)(f / ((unsigned)p.cout_pad * 27));
+      p.wf[f] = (o < p.cout && i < p.cin) ? f2bf(p.w[((size_t)o * 27 + (26 - k)) * p.cin + i])
+                                          : (uint16_t)0;
+    }
   }
 }
 

@@ -31,8 +31,7 @@ struct NetPlan {
   size_t n_params = 0;
   size_t x0 = 0, a[kNetMaxLevels] = {}, e[kNetMaxLevels] = {}, p[kNetMaxLevels] = {},
          da[kNetMaxLevels] = {}, db[kNetMaxLevels] = {};
-  size_t out = 0, ge[kNetMaxLevels] = {}, gd[kNetMaxLevels] = {}, gtmp = 0, gdx = 0, dyp = 0,
-         partials = 0, loss = 0, slabs = 0;
+  size_t out = 0, ge[kNetMaxLevels] = {}, gdx = 0, dyp[2] = {}, partials = 0, loss = 0, slabs = 0;
   size_t total_infer = 0, total_train = 0;
   int c(int l) const { return cfg.base << l; }
 };
@@ -134,19 +133,17 @@ rism3d_status net_plan(const rism3d_unet_config* cfg, int nx, int ny, int nz, Ne
   }
   P->total_infer = off;
   P->out = take(P->nvox[0] * cfg->out_channels * 4);
-  size_t max_c = 0, max_cin = 0, max_cout_pad = 0;
-  for (const NetLayer& ly : P->layers) {
-    max_c = std::max(max_c, P->nvox[ly.level] * (size_t)ly.cout);
-    max_cin = std::max(max_cin, P->nvox[ly.level] * (size_t)((ly.cin + 15) & ~15));
+  // training: the BF16 gradient of the layer at hand and of the next, the FP32
+  // gradients that cross a level (up or down), and the skip branches'
+  size_t max_dx = 4, max_cout_pad = 0;
+  for (const NetLayer& ly : P->layers)
     max_cout_pad = std::max(max_cout_pad, P->nvox[ly.level] * (size_t)ly.cout_pad);
-  }
-  for (int l = 0; l < L; ++l) {
+  for (int l = 0; l + 1 < L; ++l) {
     P->ge[l] = take(P->nvox[l] * P->c(l) * 4);
-    if (l < L - 1) P->gd[l] = take(P->nvox[l] * P->c(l) * 4);
+    max_dx = std::max(max_dx, std::max(P->nvox[l] * P->c(l + 1), P->nvox[l + 1] * P->c(l)));
   }
-  P->gtmp = take(max_c * 4);
-  P->gdx = take(max_cin * 4);
-  P->dyp = take(max_cout_pad * 2);
+  P->gdx = take(max_dx * 4);
+  for (size_t& d : P->dyp) d = take(max_cout_pad * 2);
   P->partials = take(kMsePartials * sizeof(double));
   P->loss = take(sizeof(double));
   size_t slab_floats = 0;   // the slabs of the largest layer's gradient
@@ -169,14 +166,21 @@ T* wsp(void* ws, size_t off) {
 unsigned net_blocks(size_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
 
 void net_pack(const NetPlan& P, const float* params, void* ws, bool flipped, hipStream_t s) {
-  for (const NetLayer& ly : P.layers) {
+  net::PackTable t;
+  memset(&t, 0, sizeof(t));
+  size_t most = 0;
+  for (size_t j = 0; j < P.layers.size(); ++j) {
+    const NetLayer& ly = P.layers[j];
     const int cin16 = (ly.cin + 15) & ~15;
-    const size_t n = (size_t)ly.cout_pad * 27 * ly.cin_pad +
-                     (flipped ? (size_t)cin16 * 27 * ly.cout_pad : 0);
-    hipLaunchKernelGGL(net::k_pack_weights, dim3(net_blocks(n, 256)), dim3(256), 0, s,
-                       params + ly.w_off, ly.cout, ly.cin, ly.cout_pad, ly.cin_pad, cin16,
-                       wsp<uint16_t>(ws, ly.wp), flipped ? wsp<uint16_t>(ws, ly.wf) : nullptr);
+    t.l[j] = {params + ly.w_off, wsp<uint16_t>(ws, ly.wp),
+              flipped ? wsp<uint16_t>(ws, ly.wf) : nullptr, ly.cout, ly.cin, ly.cout_pad, ly.cin_pad,
+              cin16};
+    most = std::max(most, (size_t)ly.cout_pad * 27 * (ly.cin_pad + (flipped ? cin16 : 0)));
   }
+  // four elements a thread in the largest layer; one launch instead of a layer's
+  // each, which the 4 us of a launch bounded
+  hipLaunchKernelGGL(net::k_pack_weights, dim3(net_blocks(most, 1024), (unsigned)P.layers.size()),
+                     dim3(256), 0, s, t);
 }
 
 // One convolution (channel counts are multiples of 8): the halo-tiled
@@ -216,7 +220,9 @@ net::ConvArgs conv_args(const NetPlan& P, const NetLayer& ly, void* ws, net::Con
   a.w = wsp<uint16_t>(ws, ly.wp);
   a.bias = params + ly.b_off;
   a.yb = nullptr;
-  a.yf = nullptr;
+  a.yf = a.yf2 = nullptr;
+  a.act = nullptr;
+  a.split = 0;
   a.cout = ly.cout;
   a.cout_pad = ly.cout_pad;
   a.nz = P.nz[ly.level];
@@ -266,7 +272,7 @@ void net_forward(const NetPlan& P, const float* params, const float* input, floa
                  hipStream_t s) {
   const int L = P.cfg.levels;
   const NetLayer& l0 = P.layers[0];
-  hipLaunchKernelGGL(net::k_to_channels_last, dim3(net_blocks(P.nvox[0] * l0.cin_pad, 256)),
+  hipLaunchKernelGGL(net::k_to_channels_last, dim3(net_blocks(P.nvox[0], 256)),
                      dim3(256), 0, s, input, P.cfg.in_channels, l0.cin_pad, P.nvox[0],
                      wsp<uint16_t>(ws, P.x0));
   const std::vector<net::ConvIn> in = net_inputs(P, ws);
@@ -289,23 +295,44 @@ void net_forward(const NetPlan& P, const float* params, const float* input, floa
   net_conv<net::EPI_F32_SITE>(a, s);
 }
 
-// dX of one convolution (transposed convolution of dy_pre with the flipped
-// weights) into FP32 channels last [N][cin].
-void net_conv_dx(const NetPlan& P, const NetLayer& ly, void* ws, const uint16_t* dyp, float* dx,
-                 hipStream_t s) {
+// dX of one convolution: the transposed convolution of dy_pre with the flipped
+// weights.
+net::ConvArgs conv_dx_args(const NetPlan& P, const NetLayer& ly, void* ws, const uint16_t* dyp) {
   net::ConvArgs a;
   a.in = {dyp, nullptr, ly.cout_pad, 0, 0};
   a.w = wsp<uint16_t>(ws, ly.wf);
   a.bias = nullptr;
   a.yb = nullptr;
-  a.yf = dx;
+  a.yf = a.yf2 = nullptr;
+  a.act = nullptr;
+  a.split = 0;
   a.cout = ly.cin;
   a.cout_pad = (ly.cin + 15) & ~15;
   a.nz = P.nz[ly.level];
   a.ny = P.ny[ly.level];
   a.nx = P.nx[ly.level];
-  a.slope = 0.0f;
-  net_conv<net::EPI_F32_CL>(a, s);
+  a.slope = P.cfg.slope;
+  return a;
+}
+
+// ... times the derivative of the activation act that the layer read: dy_pre of
+// the layer before, BF16.
+void net_conv_dx_leaky(const NetPlan& P, const NetLayer& ly, void* ws, const uint16_t* dyp,
+                       size_t act, uint16_t* out, hipStream_t s) {
+  net::ConvArgs a = conv_dx_args(P, ly, ws, dyp);
+  a.act = wsp<uint16_t>(ws, act);
+  a.yb = out;
+  net_conv<net::EPI_BF16_DLEAKY>(a, s);
+}
+
+// ... in FP32 channels last: the first `split` channels to dx, the others to skip.
+void net_conv_dx_split(const NetPlan& P, const NetLayer& ly, void* ws, const uint16_t* dyp, int split,
+                       float* dx, float* skip, hipStream_t s) {
+  net::ConvArgs a = conv_dx_args(P, ly, ws, dyp);
+  a.yf = dx;
+  a.yf2 = skip;
+  a.split = split;
+  net_conv<net::EPI_F32_SPLIT>(a, s);
 }
 
 // Weight and bias gradients of one layer, written to grad + w_off (b follows W).
@@ -337,13 +364,6 @@ void net_conv_dw(const NetPlan& P, const NetLayer& ly, const net::ConvIn& in, vo
                      sh.slabs, n, grad + ly.w_off);
 }
 
-void net_leaky_bwd(const NetPlan& P, size_t y_off, const float* g, int level, int C, void* ws,
-                   hipStream_t s) {
-  const size_t n = P.nvox[level] * C;
-  hipLaunchKernelGGL(net::k_leaky_bwd, dim3(net_blocks(n, 256)), dim3(256), 0, s,
-                     wsp<uint16_t>(ws, y_off), g, wsp<uint16_t>(ws, P.dyp), n, P.cfg.slope);
-}
-
 // Loss (mean squared error against target, FP32 site-major) and its
 // gradient with respect to every parameter (grad, FP32, overwritten).
 void net_gradient(const NetPlan& P, const float* params, const float* input, const float* target,
@@ -353,51 +373,50 @@ void net_gradient(const NetPlan& P, const float* params, const float* input, con
   net_forward(P, params, input, out, ws, s);
   const NetLayer& lo = P.layers.back();
   hipLaunchKernelGGL(net::k_mse, dim3(kMsePartials), dim3(256), 0, s, out, target, lo.cout,
-                     lo.cout_pad, P.nvox[0], wsp<uint16_t>(ws, P.dyp), wsp<double>(ws, P.partials));
-  hipLaunchKernelGGL(net::k_sum_partials, dim3(1), dim3(64), 0, s, wsp<double>(ws, P.partials),
+                     lo.cout_pad, P.nvox[0], wsp<uint16_t>(ws, P.dyp[0]), wsp<double>(ws, P.partials));
+  hipLaunchKernelGGL(net::k_sum_partials, dim3(1), dim3(256), 0, s, wsp<double>(ws, P.partials),
                      kMsePartials, 1.0 / ((double)lo.cout * (double)P.nvox[0]),
                      wsp<double>(ws, P.loss));
   const std::vector<net::ConvIn> in = net_inputs(P, ws);
   const std::vector<size_t> outs = net_outputs(P);
-  const uint16_t* dyp = wsp<uint16_t>(ws, P.dyp);
-  float* gtmp = wsp<float>(ws, P.gtmp);
+  // dy is the BF16 gradient before the activation of the layer at hand; every
+  // step leaves the next one's in the other buffer
+  uint16_t* dy = wsp<uint16_t>(ws, P.dyp[0]);
+  uint16_t* next = wsp<uint16_t>(ws, P.dyp[1]);
   float* gdx = wsp<float>(ws, P.gdx);
+  const float slope = P.cfg.slope;
+  // layer j: its weight gradient, then dy of layer `before` whose output it read
+  auto through = [&](size_t j, size_t before) {
+    net_conv_dw(P, P.layers[j], in[j], ws, dy, grad, s);
+    net_conv_dx_leaky(P, P.layers[j], ws, dy, outs[before], next, s);
+    std::swap(dy, next);
+  };
   const size_t jo = P.layers.size() - 1;
-  net_conv_dw(P, lo, in[jo], ws, dyp, grad, s);
-  // gradient at d_0 (or e_0 when there is a single level)
-  float* g_top = wsp<float>(ws, L >= 2 ? P.gd[0] : P.ge[0]);
-  net_conv_dx(P, lo, ws, dyp, g_top, s);
+  through(jo, jo - 1);
   for (int l = 0; l <= L - 2; ++l) {
     const size_t jb = jo - 1 - 2 * (size_t)l, ja = jb - 1;
-    const NetLayer& lb = P.layers[jb];
-    const NetLayer& la = P.layers[ja];
-    net_leaky_bwd(P, outs[jb], wsp<float>(ws, P.gd[l]), l, P.c(l), ws, s);
-    net_conv_dw(P, lb, in[jb], ws, dyp, grad, s);
-    net_conv_dx(P, lb, ws, dyp, gtmp, s);
-    net_leaky_bwd(P, outs[ja], gtmp, l, P.c(l), ws, s);
-    net_conv_dw(P, la, in[ja], ws, dyp, grad, s);
-    net_conv_dx(P, la, ws, dyp, gdx, s);
-    const int cin = la.cin, ca = P.c(l + 1);
-    hipLaunchKernelGGL(net::k_take_skip, dim3(net_blocks(P.nvox[l] * (cin - ca), 256)), dim3(256),
-                       0, s, gdx, cin, ca, wsp<float>(ws, P.ge[l]), P.nvox[l]);
-    float* gup = wsp<float>(ws, (l + 1 == L - 1) ? P.ge[L - 1] : P.gd[l + 1]);
-    hipLaunchKernelGGL(net::k_up2_bwd, dim3(net_blocks(P.nvox[l + 1] * ca, 256)), dim3(256), 0, s,
-                       gdx, cin, ca, gup, P.nz[l], P.ny[l], P.nx[l]);
+    through(jb, ja);
+    const int ca = P.c(l + 1);
+    net_conv_dw(P, P.layers[ja], in[ja], ws, dy, grad, s);
+    net_conv_dx_split(P, P.layers[ja], ws, dy, ca, gdx, wsp<float>(ws, P.ge[l]), s);
+    // the upsampled tensor is the output of the layer before (d_{l+1} or e_{L-1})
+    hipLaunchKernelGGL(net::k_up2_bwd_leaky, dim3(net_blocks(P.nvox[l + 1] * (ca / 4), 256)),
+                       dim3(256), 0, s, gdx, wsp<uint16_t>(ws, outs[ja - 1]), next, P.nz[l], P.ny[l],
+                       P.nx[l], ca, slope);
+    std::swap(dy, next);
   }
   for (int l = L - 1; l >= 0; --l) {
-    const NetLayer& lb = P.layers[2 * l + 1];
-    const NetLayer& la = P.layers[2 * l];
-    net_leaky_bwd(P, outs[2 * l + 1], wsp<float>(ws, P.ge[l]), l, P.c(l), ws, s);
-    net_conv_dw(P, lb, in[2 * l + 1], ws, dyp, grad, s);
-    net_conv_dx(P, lb, ws, dyp, gtmp, s);
-    net_leaky_bwd(P, outs[2 * l], gtmp, l, P.c(l), ws, s);
-    net_conv_dw(P, la, in[2 * l], ws, dyp, grad, s);
+    const size_t jb = 2 * (size_t)l + 1, ja = jb - 1;
+    through(jb, ja);
+    net_conv_dw(P, P.layers[ja], in[ja], ws, dy, grad, s);
     if (l > 0) {
-      net_conv_dx(P, la, ws, dyp, gdx, s);
-      const size_t n = P.nvox[l - 1] * P.c(l - 1);
-      hipLaunchKernelGGL(net::k_pool2_bwd_add, dim3(net_blocks(n, 256)), dim3(256), 0, s, gdx,
-                         wsp<float>(ws, P.ge[l - 1]), P.nz[l - 1], P.ny[l - 1], P.nx[l - 1],
-                         P.c(l - 1));
+      const int C = P.c(l - 1);
+      net_conv_dx_split(P, P.layers[ja], ws, dy, C, gdx, nullptr, s);
+      hipLaunchKernelGGL(net::k_pool2_bwd_leaky, dim3(net_blocks(P.nvox[l - 1] * (C / 4), 256)),
+                         dim3(256), 0, s, gdx, wsp<float>(ws, P.ge[l - 1]),
+                         wsp<uint16_t>(ws, outs[jb - 2]), next, P.nz[l - 1], P.ny[l - 1],
+                         P.nx[l - 1], C, slope);
+      std::swap(dy, next);
     }
   }
 }
