@@ -27,13 +27,13 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kConvThreads = 256;   // 4 waves
 
-// FP32 -> BF16 with round-to-nearest-even (NaN stays NaN); BF16 -> FP32 exact.
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)0x7fc0;
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+// FP32 -> BF16 with round-to-nearest-even (NaN stays NaN), one conversion
+// instruction for two values; BF16 -> FP32 exact.
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)lo, (__bf16)hi});
 }
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 __device__ __forceinline__ bf16x8 ld8(const uint16_t* p) {   // 16-byte aligned
@@ -42,13 +42,6 @@ __device__ __forceinline__ bf16x8 ld8(const uint16_t* p) {   // 16-byte aligned
 __device__ __forceinline__ bf16x8 zero8() {
   const u32x4 z = {0u, 0u, 0u, 0u};
   return __builtin_bit_cast(bf16x8, z);
-}
-
-// Offsets of tap k = (dz * 3 + dy) * 3 + dx are (dz - 1, dy - 1, dx - 1).
-__device__ __forceinline__ void tap_offset(int tap, int& dz, int& dy, int& dx) {
-  dz = tap / 9 - 1;
-  dy = (tap / 3) % 3 - 1;
-  dx = tap % 3 - 1;
 }
 
 // Input of a convolution: channels [0, ca) from tensor a (on the output grid,
@@ -83,7 +76,7 @@ enum ConvEpilogue {
 
 struct ConvArgs {
   ConvIn in;
-  const uint16_t* w;    // packed [cout_pad][27][cin], cin = ca + cb
+  const uint16_t* w;    // packed for cout_pad x (ca + cb) channels (k_pack_weights)
   const float* bias;    // [cout] (EPI 0, 1)
   uint16_t* yb;         // EPI_BF16_LEAKY / EPI_BF16_DLEAKY output
   float* yf;            // EPI_F32_SITE / EPI_F32_SPLIT output
@@ -98,34 +91,43 @@ struct ConvArgs {
 // d * leaky'(.) of four channels as BF16, the derivative read from the sign of the
 // BF16 activation y.
 __device__ __forceinline__ u32x2 leaky_bwd4(u32x2 y, f32x4 d, float slope) {
-  uint16_t h[4];
+  float h[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const uint16_t a = (uint16_t)(e & 1 ? y[e >> 1] >> 16 : y[e >> 1] & 0xffffu);
-    h[e] = f2bf(bf2f(a) > 0.0f ? d[e] : slope * d[e]);
+    h[e] = bf2f(a) > 0.0f ? d[e] : slope * d[e];
   }
-  return u32x2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
+  return u32x2{f2bf2(h[0], h[1]), f2bf2(h[2], h[3])};
+}
+
+// Bias of output channels c0 .. c0 + 3 (zero beyond the real ones).
+template <int EPI>
+__device__ __forceinline__ f32x4 conv_bias(const ConvArgs& p, int c0) {
+  f32x4 b = {0.f, 0.f, 0.f, 0.f};
+  if (EPI == EPI_BF16_LEAKY || EPI == EPI_F32_SITE)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (c0 + e < p.cout) b[e] = p.bias[c0 + e];
+  return b;
 }
 
 // Epilogue of one accumulator tile: output channels c0 .. c0 + 3 of voxel v.
 template <int EPI>
-__device__ __forceinline__ void conv_store(const ConvArgs& p, int N, size_t v, int c0,
-                                           const f32x4& r) {
+__device__ __forceinline__ void conv_store(const ConvArgs& p, int N, size_t v, int c0, f32x4 bias,
+                                           f32x4 r) {
   if (EPI == EPI_BF16_LEAKY) {
-    uint16_t h[4];
+    float h[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float val = r[e] + (c0 + e < p.cout ? p.bias[c0 + e] : 0.0f);
-      val = val > 0.0f ? val : p.slope * val;
-      h[e] = f2bf(val);
+      const float val = r[e] + bias[e];
+      h[e] = val > 0.0f ? val : p.slope * val;
     }
-    const u32x2 pk = {(uint32_t)h[0] | ((uint32_t)h[1] << 16),
-                      (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-    *reinterpret_cast<u32x2*>(p.yb + v * p.cout_pad + c0) = pk;
+    *reinterpret_cast<u32x2*>(p.yb + v * p.cout_pad + c0) =
+        u32x2{f2bf2(h[0], h[1]), f2bf2(h[2], h[3])};
   } else if (EPI == EPI_F32_SITE) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (c0 + e < p.cout) p.yf[(size_t)(c0 + e) * N + v] = r[e] + p.bias[c0 + e];
+      if (c0 + e < p.cout) p.yf[(size_t)(c0 + e) * N + v] = r[e] + bias[e];
   } else if (EPI == EPI_BF16_DLEAKY) {
     const u32x2 y = *reinterpret_cast<const u32x2*>(p.act + v * p.cout + c0);
     *reinterpret_cast<u32x2*>(p.yb + v * p.cout + c0) = leaky_bwd4(y, r, p.slope);
@@ -137,23 +139,47 @@ __device__ __forceinline__ void conv_store(const ConvArgs& p, int N, size_t v, i
 }
 
 // Convolutions with 8 * CG input channels on a halo-tiled grid: a workgroup
-// computes 16 output channels (tile blockIdx.y) of a 16 x TY x 4 voxel tile
-// (TY = 8; 2 on small grids, for more workgroups).  It stages the tile's input
-// with a one-voxel halo (18 x (TY + 2) x 6 voxels) in LDS, CGC channel groups at a
-// time (CG / CGC chunks), and every tap's operand is read from there instead
-// of from the cache hierarchy.  LDS layout [hz][hy][cg][hx] (16-byte units):
-// the 16 voxels of one operand are consecutive units, conflict-free.  Wave w
-// owns the z-slice z0 + w: its TY rows y0 .. y0 + TY - 1 of 16 voxels are its
-// TY accumulator tiles.  Within a chunk the K steps take (tap, channel group)
-// pairs in tap-major order, four per matrix instruction: lane group g
-// supplies pair q0 + g (its 8 channels), the weights are the A operand (rows
-// = output channels), the voxels the B operand (columns).
+// computes MT tiles of 16 output channels (from MT blockIdx.y) of a 16 x TY x 4
+// voxel tile (TY = 8; 2 on small grids, for more workgroups).  It stages the
+// tile's input with a one-voxel halo (18 x (TY + 2) x 6 voxels) in LDS, CGC channel
+// groups at a time (CG / CGC chunks), and every tap's operand is read from there
+// instead of from the cache hierarchy.  LDS layout [hz][hy][cg][hx] (16-byte
+// units): the 16 voxels of one operand are consecutive units, conflict-free.  Wave
+// w owns the z-slice z0 + w: its TY rows y0 .. y0 + TY - 1 of 16 voxels are its TY
+// accumulator tiles per output tile.  Within a chunk the K steps take (tap, channel
+// group) pairs in tap-major order, four per matrix instruction: lane group g
+// supplies pair q0 + g (its 8 channels), the weights are the A operand (rows =
+// output channels), the voxels the B operand (columns).  The weights are packed in
+// this order (k_pack_weights), so a step's A operand is one coalesced load at a
+// fixed offset, and the halo offsets of the steps are formed once.
+//
+// Bound by the LDS reads: an operand of 1 KB feeds MT instructions of 16 cycles
+// on each of four SIMDs, so one output tile can reach half of the matrix rate and
+// two all of it; below that by staging, whose index arithmetic and latency are
+// kept small (one row of the halo per thread group, loads in batches, three waves
+// a SIMD).  Before and after, at 128^3: 16 -> 16 channels 78 -> 52 us, 48 -> 16 215
+// -> 121 us (0.29 of the BF16 peak), and at 64^3 96 -> 32 136 -> 45 us (0.39).
 constexpr int kTileX = 16, kTileZ = 4;
 constexpr int kHaloX = kTileX + 2, kHaloZ = kTileZ + 2;
 
-template <int EPI, int CGC, int TY>
-__global__ __launch_bounds__(kConvThreads) void k_conv3(ConvArgs p) {
-  constexpr int kTileY = TY, kHaloY = TY + 2;
+// K steps of a chunk of CGC channel groups
+__host__ __device__ constexpr int conv_steps(int cgc) { return (27 * cgc + 3) / 4; }
+// channel groups a chunk takes out of cg: the largest of 4, 3, 2, 1 that divides it
+__host__ __device__ constexpr int conv_chunk(int cg) {
+  return cg % 4 == 0 ? 4 : cg % 3 == 0 ? 3 : cg % 2 == 0 ? 2 : 1;
+}
+// elements of the packed weights of cout (a multiple of 16) x cin (of 8) channels
+__host__ __device__ constexpr size_t conv_packed(int cout, int cin) {
+  return (size_t)(cout / 16) * (cin / 8 / conv_chunk(cin / 8)) * conv_steps(conv_chunk(cin / 8)) * 512;
+}
+
+// staging loads a thread has in flight, out of n: in as few batches of at most 9
+__host__ __device__ constexpr int conv_batch(int n) { return (n + (n + 8) / 9 - 1) / ((n + 8) / 9); }
+
+template <int EPI, int CGC, int TY, int MT>
+__global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(3)))
+void k_conv3(ConvArgs p) {
+  constexpr int kTileY = TY, kHaloY = TY + 2, NQ = 27 * CGC, NS = conv_steps(CGC);
   __shared__ __align__(16) u32x4 halo[kHaloZ * kHaloY * CGC * kHaloX];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = lane & 15, g = lane >> 4;
@@ -165,50 +191,81 @@ __global__ __launch_bounds__(kConvThreads) void k_conv3(ConvArgs p) {
   b /= tiles_x;
   const int y0 = (b % tiles_y) * kTileY;
   const int z0 = (b / tiles_y) * kTileZ;
-  const int cbase = (int)blockIdx.y * 16;
-  f32x4 acc[kTileY];
+  f32x4 acc[MT][kTileY];
 #pragma unroll
-  for (int t = 0; t < kTileY; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  constexpr int nq = 27 * CGC;
-  const size_t wrow = (size_t)27 * CG * 8;
-  for (int c0 = 0; c0 < CG; c0 += CGC) {
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int t = 0; t < kTileY; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int off[NS];   // halo unit of row 0 of this lane's pair in each step
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int q = 4 * s + g < NQ ? 4 * s + g : 0;
+    const int tap = q / CGC, cg = q - tap * CGC;
+    off[s] = (((wave + tap / 9) * kHaloY + tap / 3 % 3) * CGC + cg) * kHaloX + j + tap % 3;
+  }
+  const int chunks = CG / CGC;
+  const u32x4* aw = reinterpret_cast<const u32x4*>(p.w) +
+                    (size_t)blockIdx.y * MT * chunks * NS * 64 + lane;
+  for (int c0 = 0; c0 < CG; c0 += CGC, aw += NS * 64) {
     if (c0 > 0) __syncthreads();   // the previous chunk's operands are read
-    // stage: item (h, cg), channel group fastest (consecutive 16-byte reads)
-    for (int it = threadIdx.x; it < kHaloZ * kHaloY * kHaloX * CGC; it += kConvThreads) {
-      const int h = it / CGC, cg = it - h * CGC;
-      const int hx = h % kHaloX, hy = (h / kHaloX) % kHaloY, hz = h / (kHaloX * kHaloY);
-      const bf16x8 v =
-          load_in(p.in, c0 + cg, z0 + hz - 1, y0 + hy - 1, x0 + hx - 1, p.nz, p.ny, p.nx);
-      halo[((hz * kHaloY + hy) * CGC + cg) * kHaloX + hx] = __builtin_bit_cast(u32x4, v);
-    }
-    __syncthreads();
-    for (int q0 = 0; q0 < nq; q0 += 4) {
-      const int q = q0 + g;
-      bf16x8 aw = zero8(), bx[kTileY];
-      if (q < nq) {
-        const int tap = q / CGC, cg = q - tap * CGC;
-        int dz, dy, dx;
-        tap_offset(tap, dz, dy, dx);
-        aw = ld8(p.w + (size_t)(cbase + j) * wrow + (size_t)(tap * CG + c0 + cg) * 8);
-        const int base = ((wave + dz + 1) * kHaloY + dy + 1) * CGC + cg;
+    // stage: a thread keeps its x and channel group and takes every RP-th row (hz,
+    // hy); x is the fastest lane index, so the LDS stores are conflict-free.  A
+    // batch's loads are all in flight before its first store.
+    constexpr int RT = kHaloX * CGC, RP = kConvThreads / RT, ROWS = kHaloZ * kHaloY;
+    constexpr int ALL = (ROWS + RP - 1) / RP, B = conv_batch(ALL);
+    const int rr = threadIdx.x / RT, l = threadIdx.x - rr * RT;
+    const int cg = l / kHaloX, hx = l - cg * kHaloX, x = x0 + hx - 1;
+    const int c = (c0 + cg) * 8;
+    const bool skip = c >= p.in.ca;
+    const int up = skip ? 0 : p.in.up_a, C = skip ? p.in.cb : p.in.ca;
+    const int ny = p.ny >> up, nx = p.nx >> up;
+    const uint16_t* src = (skip ? p.in.b + (c - p.in.ca) : p.in.a + c) + (size_t)(x >> up) * C;
+    const bool in_x = rr < RP && (unsigned)x < (unsigned)p.nx;
+    for (int i0 = 0; i0 < ALL; i0 += B) {
+      u32x4 v[B];
 #pragma unroll
-        for (int t = 0; t < kTileY; ++t)
-          bx[t] = __builtin_bit_cast(bf16x8, halo[(base + t * CGC) * kHaloX + j + dx + 1]);
-      } else {
-#pragma unroll
-        for (int t = 0; t < kTileY; ++t) bx[t] = zero8();
+      for (int i = 0; i < B; ++i) {
+        const int row = rr + (i0 + i) * RP, hz = row / kHaloY, hy = row - hz * kHaloY;
+        const int z = z0 + hz - 1, y = y0 + hy - 1;
+        v[i] = u32x4{0u, 0u, 0u, 0u};
+        if (in_x && (unsigned)z < (unsigned)p.nz && (unsigned)y < (unsigned)p.ny)
+          v[i] = *reinterpret_cast<const u32x4*>(
+              src + (size_t)(unsigned)((z >> up) * ny + (y >> up)) * (unsigned)(nx * C));
       }
 #pragma unroll
-      for (int t = 0; t < kTileY; ++t)
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw, bx[t], acc[t], 0, 0, 0);
+      for (int i = 0; i < B; ++i) {
+        const int row = rr + (i0 + i) * RP;
+        if (rr < RP && row < ROWS) halo[(row * CGC + cg) * kHaloX + hx] = v[i];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      bf16x8 a[MT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        a[m] = __builtin_bit_cast(bf16x8, aw[(size_t)(m * chunks) * NS * 64 + s * 64]);
+#pragma unroll
+      for (int t = 0; t < kTileY; ++t) {
+        u32x4 v = halo[off[s] + t * CGC * kHaloX];
+        if (4 * s + 4 > NQ && 4 * s + g >= NQ) v = u32x4{0u, 0u, 0u, 0u};   // beyond the last pair
+        const bf16x8 x = __builtin_bit_cast(bf16x8, v);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+          acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], x, acc[m][t], 0, 0, 0);
+      }
     }
   }
   const int x = x0 + j, z = z0 + wave;
+  if (x >= p.nx || z >= p.nz) return;
 #pragma unroll
-  for (int t = 0; t < kTileY; ++t) {
-    const int y = y0 + t;
-    if (x < p.nx && y < p.ny && z < p.nz)
-      conv_store<EPI>(p, N, ((size_t)z * p.ny + y) * p.nx + x, cbase + 4 * g, acc[t]);
+  for (int m = 0; m < MT; ++m) {
+    const int ch = ((int)blockIdx.y * MT + m) * 16 + 4 * g;
+    const f32x4 bias = conv_bias<EPI>(p, ch);
+#pragma unroll
+    for (int t = 0; t < kTileY; ++t)
+      if (y0 + t < p.ny)
+        conv_store<EPI>(p, N, ((size_t)z * p.ny + y0 + t) * p.nx + x, ch, bias, acc[m][t]);
   }
 }
 
@@ -283,26 +340,52 @@ __global__ __launch_bounds__(kConvThreads) void k_conv3_wgrad(WgradArgs p) {
   for (int t = (int)blockIdx.x * p.per; t < t_end; ++t) {
     const int x0 = t % tx * kWgX, y0 = t / tx % ty * kWgY, z0 = t / (tx * ty) * kWgZ;
     __syncthreads();   // the previous tile's operands are read
-    for (int it = threadIdx.x; it < kWgX * kWgZ * (kWgY / 2) * 2 * OT; it += kConvThreads) {
+    // every load of the tile in flight before the first LDS store
+    constexpr int ND = kWgX * kWgZ * (kWgY / 2) * 2 * OT / kConvThreads;
+    constexpr int NX = (kWgRows * (kWgY / 2 + 1) * 2 + kConvThreads - 1) / kConvThreads;
+    bf16x8 vd[ND][2], vx[NX][2];
+#pragma unroll
+    for (int k = 0; k < ND; ++k) {
+      const int it = threadIdx.x + k * kConvThreads;
       const int cg = it % (2 * OT), r = it / (2 * OT);
       const int xx = r % kWgX, yp = r / kWgX % (kWgY / 2), zz = r / (kWgX * (kWgY / 2));
       const int x = x0 + xx, y = y0 + 2 * yp, z = z0 + zz, o = o0 + cg * 8;
-      bf16x8 a = zero8(), b = zero8();
+      vd[k][0] = vd[k][1] = zero8();
       if (x < p.nx && z < p.nz && o < p.cout_pad) {
         const uint16_t* q = p.dy + (((size_t)z * p.ny + y) * p.nx + x) * p.cout_pad + o;
-        if (y < p.ny) a = ld8(q);
-        if (y + 1 < p.ny) b = ld8(q + (size_t)p.nx * p.cout_pad);
+        if (y < p.ny) vd[k][0] = ld8(q);
+        if (y + 1 < p.ny) vd[k][1] = ld8(q + (size_t)p.nx * p.cout_pad);
       }
-      store_pair(ds + cg * 8 * kWgDyPitch + (zz * kWgX + xx) * 4 + yp, kWgDyPitch, a, b);
     }
-    for (int it = threadIdx.x; it < kWgRows * (kWgY / 2 + 1) * cgi; it += kConvThreads) {
-      const int cg = it % cgi, r = it / cgi;
+    // (an 8-channel input tile repeats its group in rows that no result reads)
+#pragma unroll
+    for (int k = 0; k < NX; ++k) {
+      const int it = threadIdx.x + k * kConvThreads;
+      const int cg = it % 2 < cgi ? it % 2 : 0, r = it / 2;
       const int hx = r % (kWgX + 2), q = r / (kWgX + 2);
       const int yp = q % (kWgY / 2 + 1), hz = q / (kWgY / 2 + 1);
       const int x = x0 + hx - 1, y = y0 + 2 * yp - 1, z = z0 + hz - 1;
-      const bf16x8 a = load_in(p.in, ti * 2 + cg, z, y, x, p.nz, p.ny, p.nx);
-      const bf16x8 b = load_in(p.in, ti * 2 + cg, z, y + 1, x, p.nz, p.ny, p.nx);
-      store_pair(xs + cg * 8 * kWgXPitch + (hz * (kWgX + 2) + hx) * 6 + yp, kWgXPitch, a, b);
+      if (hz < kWgZ + 2) {
+        vx[k][0] = load_in(p.in, ti * 2 + cg, z, y, x, p.nz, p.ny, p.nx);
+        vx[k][1] = load_in(p.in, ti * 2 + cg, z, y + 1, x, p.nz, p.ny, p.nx);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < ND; ++k) {
+      const int it = threadIdx.x + k * kConvThreads;
+      const int cg = it % (2 * OT), r = it / (2 * OT);
+      const int xx = r % kWgX, yp = r / kWgX % (kWgY / 2), zz = r / (kWgX * (kWgY / 2));
+      store_pair(ds + cg * 8 * kWgDyPitch + (zz * kWgX + xx) * 4 + yp, kWgDyPitch, vd[k][0], vd[k][1]);
+    }
+#pragma unroll
+    for (int k = 0; k < NX; ++k) {
+      const int it = threadIdx.x + k * kConvThreads;
+      const int cg = it % 2, r = it / 2;
+      const int hx = r % (kWgX + 2), q = r / (kWgX + 2);
+      const int yp = q % (kWgY / 2 + 1), hz = q / (kWgY / 2 + 1);
+      if (hz < kWgZ + 2)
+        store_pair(xs + cg * 8 * kWgXPitch + (hz * (kWgX + 2) + hx) * 6 + yp, kWgXPitch, vx[k][0],
+                   vx[k][1]);
     }
     __syncthreads();
 #pragma unroll 1
@@ -422,7 +505,7 @@ __global__ void k_pool2(const uint16_t* __restrict__ in, uint16_t* __restrict__ 
   u32x4 o;
 #pragma unroll
   for (int e = 0; e < 4; ++e)
-    o[e] = (uint32_t)f2bf(0.125f * s[2 * e]) | ((uint32_t)f2bf(0.125f * s[2 * e + 1]) << 16);
+    o[e] = f2bf2(0.125f * s[2 * e], 0.125f * s[2 * e + 1]);
   *reinterpret_cast<u32x4*>(out + cv * C + g * 8) = o;
 }
 
@@ -475,9 +558,9 @@ __global__ void k_to_channels_last(const float* __restrict__ in, int C, int cpad
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int c = c0 + 2 * e;
-      const uint32_t a = c < C ? f2bf(in[(size_t)c * N + v]) : 0u;
-      const uint32_t b = c + 1 < C ? f2bf(in[(size_t)(c + 1) * N + v]) : 0u;
-      o[e] = a | (b << 16);
+      const float a = c < C ? in[(size_t)c * N + v] : 0.0f;
+      const float b = c + 1 < C ? in[(size_t)(c + 1) * N + v] : 0.0f;
+      o[e] = f2bf2(a, b);
     }
     *reinterpret_cast<u32x4*>(out + v * cpad + c0) = o;
   }
@@ -503,7 +586,9 @@ __global__ __launch_bounds__(256) void k_mse(const float* __restrict__ out,
           const size_t i = (size_t)(c0 + e) * N + v;
           const double d = (double)out[i] - (double)target[i];
           s += d * d;
-          o[e >> 1] |= (uint32_t)f2bf((float)(scale * d)) << (16 * (e & 1));
+          float gv = (float)(scale * d);
+          asm("" : "+v"(gv));   // rounded to FP32 first: the compiler would round once, to BF16
+          o[e >> 1] |= (uint32_t)f2bf(gv) << (16 * (e & 1));
         }
       }
       *reinterpret_cast<u32x4*>(grad + v * cpad + c0) = o;
@@ -527,10 +612,12 @@ __global__ __launch_bounds__(256) void k_sum_partials(const double* __restrict__
   if (threadIdx.x == 0) *out = scale * (red[0] + red[1] + red[2] + red[3]);
 }
 
-// FP32 master weights W[cout][27][cin] -> BF16 packed [cout_pad][27][cin_pad]
-// (forward) and flipped [cin_pad16][27][cout_pad] with tap k -> 26 - k
-// (backward data: the transposed convolution is a convolution with these), every
-// layer in one launch (blockIdx.y).
+// FP32 master weights W[cout][27][cin] -> BF16 A operands of k_conv3, [output tile]
+// [chunk][step][lane][8]: the 8 input channels of pair 4 step + g of output
+// channel 16 tile + j (zeros beyond the last pair and the real channels).  wp: the
+// forward convolution; wf: backward data, which is a convolution with outputs and
+// inputs exchanged and tap k -> 26 - k.  Every layer in one launch (blockIdx.y),
+// one lane's 16 bytes a thread.
 constexpr int kNetMaxLayers = 23;   // six levels: 12 + 10 + 1
 struct PackLayer {
   const float* w;
@@ -542,23 +629,25 @@ struct PackTable {
 };
 __global__ void k_pack_weights(PackTable t) {
   const PackLayer& p = t.l[blockIdx.y];
-  const unsigned nfwd = (unsigned)p.cout_pad * 27 * p.cin_pad;
-  const unsigned nflip = p.wf ? (unsigned)p.cin_pad16 * 27 * p.cout_pad : 0;
-  for (unsigned id = blockIdx.x * blockDim.x + threadIdx.x; id < nfwd + nflip;
+  const unsigned nf = (unsigned)(conv_packed(p.cout_pad, p.cin_pad) / 8);
+  const unsigned nb = p.wf ? (unsigned)(conv_packed(p.cin_pad16, p.cout_pad) / 8) : 0;
+  for (unsigned id = blockIdx.x * blockDim.x + threadIdx.x; id < nf + nb;
        id += gridDim.x * blockDim.x) {
-    if (id < nfwd) {
-      const int i = (int)(id % p.cin_pad);
-      const int k = (int)((id / p.cin_pad) % 27);
-      const int o = (int)(id / ((unsigned)p.cin_pad * 27));
-      p.wp[id] = (o < p.cout && i < p.cin) ? f2bf(p.w[((size_t)o * 27 + k) * p.cin + i]) : (uint16_t)0;
-    } else {
-      const unsigned f = id - nfwd;
-      const int o = (int)(f % p.cout_pad);
-      const int k = (int)((f / p.cout_pad) % 27);
-      const int i = (int)(f / ((unsigned)p.cout_pad * 27));
-      p.wf[f] = (o < p.cout && i < p.cin) ? f2bf(p.w[((size_t)o * 27 + (26 - k)) * p.cin + i])
-                                          : (uint16_t)0;
+    const bool fwd = id < nf;
+    const unsigned u = fwd ? id : id - nf;
+    const int cg_all = (fwd ? p.cin_pad : p.cout_pad) / 8, cgc = conv_chunk(cg_all);
+    const int ns = conv_steps(cgc), chunks = cg_all / cgc;
+    const int lane = u & 63, s = u / 64 % ns, chunk = u / 64 / ns % chunks, tile = u / 64 / ns / chunks;
+    const int q = 4 * s + (lane >> 4), row = tile * 16 + (lane & 15);
+    const int tap = q / cgc, col0 = (chunk * cgc + q - tap * cgc) * 8;
+    uint32_t h[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int o = fwd ? row : col0 + e, i = fwd ? col0 + e : row, k = fwd ? tap : 26 - tap;
+      h[e] = q < 27 * cgc && o < p.cout && i < p.cin ? f2bf(p.w[((size_t)o * 27 + k) * p.cin + i]) : 0u;
     }
+    reinterpret_cast<u32x4*>(fwd ? p.wp : p.wf)[u] =
+        u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
   }
 }
 

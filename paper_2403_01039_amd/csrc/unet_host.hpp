@@ -118,8 +118,8 @@ rism3d_status net_plan(const rism3d_unet_config* cfg, int nx, int ny, int nz, Ne
     return o;
   };
   for (NetLayer& ly : P->layers) {
-    ly.wp = take((size_t)ly.cout_pad * 27 * ly.cin_pad * 2);
-    ly.wf = take((size_t)((ly.cin + 15) & ~15) * 27 * ly.cout_pad * 2);
+    ly.wp = take(net::conv_packed(ly.cout_pad, ly.cin_pad) * 2);
+    ly.wf = take(net::conv_packed((ly.cin + 15) & ~15, ly.cout_pad) * 2);
   }
   P->x0 = take(P->nvox[0] * P->layers[0].cin_pad * 2);
   for (int l = 0; l < L; ++l) {
@@ -175,23 +175,32 @@ void net_pack(const NetPlan& P, const float* params, void* ws, bool flipped, hip
     t.l[j] = {params + ly.w_off, wsp<uint16_t>(ws, ly.wp),
               flipped ? wsp<uint16_t>(ws, ly.wf) : nullptr, ly.cout, ly.cin, ly.cout_pad, ly.cin_pad,
               cin16};
-    most = std::max(most, (size_t)ly.cout_pad * 27 * (ly.cin_pad + (flipped ? cin16 : 0)));
+    most = std::max(most, net::conv_packed(ly.cout_pad, ly.cin_pad) +
+                              (flipped ? net::conv_packed(cin16, ly.cout_pad) : 0));
   }
-  // four elements a thread in the largest layer; one launch instead of a layer's
-  // each, which the 4 us of a launch bounded
-  hipLaunchKernelGGL(net::k_pack_weights, dim3(net_blocks(most, 1024), (unsigned)P.layers.size()),
+  // (one launch instead of a layer's each, which the 4 us of a launch bounded)
+  hipLaunchKernelGGL(net::k_pack_weights, dim3(net_blocks(most / 8, 256), (unsigned)P.layers.size()),
                      dim3(256), 0, s, t);
 }
 
 // One convolution (channel counts are multiples of 8): the halo-tiled
-// kernel, staging CGC <= 4 channel groups (at most 64 KB of LDS) at a time,
-// CGC the largest of 4, 3, 2, 1 that divides the group count.  Tiles of
-// 16 x 8 x 4 voxels, or 16 x 2 x 4 where those would give fewer than 512
-// workgroups (the coarse levels).
+// kernel, staging conv_chunk() channel groups (at most 64 KB of LDS) at a time.
+// Tiles of 16 x 8 x 4 voxels, or 16 x 2 x 4 where those would give fewer than 512
+// workgroups (the coarse levels); two output tiles a workgroup where that leaves
+// 512 workgroups (64^3, 96 -> 32 channels: 85 us with one, 45 with two; three, for
+// 16 -> 48 at 128^3, take 234 us against 145 with one, their accumulators spill).
+template <int EPI, int CGC, int TY, int MT>
+void net_conv_mt(const net::ConvArgs& a, unsigned tiles, hipStream_t s) {
+  hipLaunchKernelGGL((net::k_conv3<EPI, CGC, TY, MT>), dim3(tiles, (unsigned)a.cout_pad / 16 / MT),
+                     dim3(net::kConvThreads), 0, s, a);
+}
+
 template <int EPI, int CGC, int TY>
 void net_conv_tiles(const net::ConvArgs& a, unsigned tiles, hipStream_t s) {
-  hipLaunchKernelGGL((net::k_conv3<EPI, CGC, TY>), dim3(tiles, a.cout_pad / 16),
-                     dim3(net::kConvThreads), 0, s, a);
+  const unsigned cot = (unsigned)a.cout_pad / 16;
+  if constexpr (EPI != net::EPI_F32_SITE)
+    if (cot % 2 == 0 && tiles * (cot / 2) >= 512) return net_conv_mt<EPI, CGC, TY, 2>(a, tiles, s);
+  net_conv_mt<EPI, CGC, TY, 1>(a, tiles, s);
 }
 
 template <int EPI, int CGC>
@@ -206,11 +215,12 @@ void net_conv_chunks(const net::ConvArgs& a, hipStream_t s) {
 
 template <int EPI>
 void net_conv(const net::ConvArgs& a, hipStream_t s) {
-  const int cg = (a.in.ca + a.in.cb) / 8;
-  if (cg % 4 == 0) net_conv_chunks<EPI, 4>(a, s);
-  else if (cg % 3 == 0) net_conv_chunks<EPI, 3>(a, s);
-  else if (cg % 2 == 0) net_conv_chunks<EPI, 2>(a, s);
-  else net_conv_chunks<EPI, 1>(a, s);
+  switch (net::conv_chunk((a.in.ca + a.in.cb) / 8)) {
+    case 4: net_conv_chunks<EPI, 4>(a, s); break;
+    case 3: net_conv_chunks<EPI, 3>(a, s); break;
+    case 2: net_conv_chunks<EPI, 2>(a, s); break;
+    default: net_conv_chunks<EPI, 1>(a, s); break;
+  }
 }
 
 net::ConvArgs conv_args(const NetPlan& P, const NetLayer& ly, void* ws, net::ConvIn in,

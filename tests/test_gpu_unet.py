@@ -172,19 +172,21 @@ def test_gradient_matches_oracle_with_bf16_rounding(R, monkeypatch):
 
 
 # Ragged voxel tiles in every axis, grids below one tile, one and two output
-# tiles a workgroup, and (one level, 576 voxel tiles) two voxel tiles a workgroup.
-@pytest.mark.parametrize("levels,shape", [(3, (8, 24, 40)), (3, (4, 12, 20)), (2, (16, 16, 16)),
-                                          (1, (72, 64, 64))])
-def test_gradient_on_ragged_tiles(R, monkeypatch, levels, shape):
+# tiles a workgroup, (one level, 576 voxel tiles) two voxel tiles a workgroup, and
+# (base 32 at 64^3) convolutions with two output tiles a workgroup on both tilings.
+@pytest.mark.parametrize("levels,base,shape", [(3, 16, (8, 24, 40)), (3, 16, (4, 12, 20)),
+                                               (2, 48, (16, 16, 16)), (1, 16, (72, 64, 64)),
+                                               (2, 32, (64, 64, 64))])
+def test_gradient_on_ragged_tiles(R, monkeypatch, levels, base, shape):
     """A network whose convolutions add three inputs with weights +-1, on small
     integers with slope 1/4: every FP32 sum up to a BF16 rounding is then exact,
     so the rounded values are those of the oracle with the same roundings, and
     the gradients differ by the FP32 sum over the N voxels alone, 2^-24 of its
     partial sums (about sqrt(N) terms large): 1e-4 of the layer's largest."""
     from oracle import unet as U
-    print(f"unet gradient levels={levels} {shape}", flush=True)
-    cfg = R.unet_config(3, 3, levels=levels, base=16, slope=0.25)
-    ocfg = U.Config(levels=levels, base=16, in_channels=3, out_channels=3, slope=0.25)
+    print(f"unet gradient levels={levels} base={base} {shape}", flush=True)
+    cfg = R.unet_config(3, 3, levels=levels, base=base, slope=0.25)
+    ocfg = U.Config(levels=levels, base=base, in_channels=3, out_channels=3, slope=0.25)
     rng = np.random.default_rng(61)
     parts = []
     for _, ci, co in ocfg.layers():
