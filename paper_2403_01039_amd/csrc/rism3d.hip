@@ -617,13 +617,14 @@ void launch_fixed_n(const Layout& L, C* spec, const C* tw, int forward, const in
                      spec, L.nx, L.ny, L.nz, L.npair, tw, forward, done, bt.stride);
 }
 
-// y pass of the FP32 iterations with a tuned width (lines = 0: default).
+// y pass of the FP32 iterations with a tuned width.  lines = 0: 16, a whole
+// 128-byte line of each row (5 sites at 128^3: 16.3 us, 32 lines 19.7, 8 lines
+// 26.9; 3 sites at 64^3 4.0, 4.2, 5.6; at 256^3 82, 103, 112).
 template <int N>
 void launch_y32_n(const Layout& L, float2* spec, const float2* tw, int forward, const int* done,
                   hipStream_t s, Batch bt, int lines) {
   switch (lines) {
     case 8: launch_fixed_n<float2, N, 1, 8>(L, spec, tw, forward, done, s, bt); break;
-    case 16: launch_fixed_n<float2, N, 1, 16>(L, spec, tw, forward, done, s, bt); break;
     case 32:
       if constexpr (N <= 256) {
         launch_fixed_n<float2, N, 1, 32>(L, spec, tw, forward, done, s, bt);
@@ -636,7 +637,7 @@ void launch_y32_n(const Layout& L, float2* spec, const float2* tw, int forward, 
         break;
       }
       [[fallthrough]];
-    default: launch_fixed_n<float2, N, 1>(L, spec, tw, forward, done, s, bt); break;
+    default: launch_fixed_n<float2, N, 1, 16>(L, spec, tw, forward, done, s, bt); break;
   }
 }
 
@@ -750,6 +751,20 @@ void launch_zcz_b(const Layout& L, void* ws, double inv_dkt, const int* done, hi
                      bt.stride);
 }
 
+// Default columns a side of the FP32 z kernel.  Tiles of 24 to 32 columns in all
+// leave several workgroups a CU to overlap the phases of (3 sites: at 64^3 6.8 us,
+// 16 columns a side 9.7; at 96^3 19.3, 20.4; 5 sites at 128^3: 4 columns a side 35.9,
+// 8 columns 40.2).  Elsewhere a narrower tile fills no whole round of a workgroup's
+// butterflies, whose guarded code rounds differently in the last bit, which a solve
+// carries to its tolerance; the widest tile in 64 KB stays (5 sites at 64^3: 15.2,
+// 4 columns 8.3).
+template <int NZ, int NV>
+constexpr int zcz32_cols() {
+  constexpr int P = (NV + 1) / 2;
+  return P == 2 && NZ <= 128 ? 8 : P == 3 && (NZ == 96 || NZ == 128) ? 4
+                                                                     : zcz_cols<float2, NZ, NV>();
+}
+
 // FP32 z kernel with a tuned width (cols = 0: default); widths whose tile
 // would exceed 120 KB of LDS are not compiled and fall back to the default.
 template <typename C, int NZ, int NV>
@@ -762,8 +777,10 @@ void launch_zcz_n(const Layout& L, void* ws, double inv_dkt, const int* done, hi
       if (cols == 8) { launch_zcz_b<C, NZ, NV, 8>(L, ws, inv_dkt, done, s, bt); return; }
     if constexpr (per_col * 16 <= 122880)
       if (cols == 16) { launch_zcz_b<C, NZ, NV, 16>(L, ws, inv_dkt, done, s, bt); return; }
+    launch_zcz_b<C, NZ, NV, zcz32_cols<NZ, NV>()>(L, ws, inv_dkt, done, s, bt);
+  } else {
+    launch_zcz_b<C, NZ, NV>(L, ws, inv_dkt, done, s, bt);
   }
-  launch_zcz_b<C, NZ, NV>(L, ws, inv_dkt, done, s, bt);
 }
 
 template <typename C, int NZ>
@@ -851,14 +868,19 @@ void launch_fused_l(const Layout& L, void* ws, const rism3d_opts* op, bool first
   }
 }
 
-// FP32 fused kernels with a tuned row count (lines = 0: default); counts
-// whose LDS tile would exceed 64 KB are not compiled and run the default.
+// FP32 fused kernels with a tuned row count (lines = 0: default); counts whose
+// LDS tile would exceed 64 KB are not compiled and run the default: fixed_lines,
+// but 8 rows for the update of short rows, where wide tiles leave too few
+// workgroups to keep the history loads in flight (64^3, MDIIS depth 5: 3 sites
+// 9.5 us, 64 rows 20.1; 5 sites 14.6, 22.1).  At 128 points 8 rows would give 60
+// for 64 us and round differently.  The residual's row count fixes the order of the
+// Gram sums and so belongs to the results.
 template <bool ANCHOR, int N>
 void launch_fused_n(const Layout& L, void* ws, const rism3d_opts* op, bool first_half,
                     hipStream_t s, Batch bt, int lines, bool control) {
   if constexpr (!ANCHOR) {
     constexpr int row = Lds<N>::PITCH * (int)sizeof(float2);
-    if (lines == 8) {
+    if (lines == 8 || (lines == 0 && first_half && N <= 64)) {
       launch_fused_l<false, N, 8>(L, ws, op, first_half, s, bt, control);
       return;
     }

@@ -195,6 +195,24 @@ def test_maps_at_flexible_lengths(R, O, saline, shape, closure):
     assert np.abs(res - ref).max() < 2e-6 * max(1.0, np.abs(ref).max())
 
 
+# Remainders of the default tiles on fixed lengths: 180 x rows against 8, y lines
+# against 16, z columns against 8 (3 sites) and 4 (5 sites).
+@pytest.mark.parametrize("saline,shape", [(True, (10, 6, 64)), (True, (6, 10, 32)),
+                                          (False, (64, 64, 20)), (True, (128, 32, 18)),
+                                          (True, (96, 96, 30)), (False, (128, 128, 36))])
+def test_map_increment_at_tile_remainders(R, O, saline, shape):
+    """The FP32 increment kernels against the oracle's map; bar of
+    test_map_increment_matches_oracle."""
+    prob, s, sys_ = _map_case(R, O, saline, shape, "kh")
+    print(f"map increment {shape} saline={saline}", flush=True)
+    rng = np.random.default_rng(23)
+    tau = (0.05 * rng.standard_normal(sys_.f.shape)).astype(np.float32)
+    delta = (0.02 * rng.standard_normal(sys_.f.shape)).astype(np.float32)
+    ref, _, _ = O.rism_map(sys_, tau.astype(np.float64) + delta.astype(np.float64) + sys_.f)
+    res = s.map_increment(torch.tensor(tau, device="cuda"), torch.tensor(delta, device="cuda"))[0]
+    assert np.abs(res.cpu().numpy() - ref).max() < 2e-6 * max(1.0, np.abs(ref).max())
+
+
 @pytest.mark.parametrize("saline,shape,closure",
                          [(sal, shp, "kh") for sal, shp in MAP_SHAPES]
                          + [(False, (64, 24, 32), "pse"), (True, (32, 16, 64), "hnc"),
