@@ -377,6 +377,64 @@ __device__ inline double block_sum(double v, double* lds) {
   return s;
 }
 
+// What the FP32 residual of V consecutive points of a pair reads besides the
+// transform.  Bound by memory: both sites' loads are in flight before the first is
+// used (site after site: 3 sites at 64^3 13.9 us, now 13.4; 5 sites at 128^3 63.8,
+// 61.2; 3 sites at 256^3, depth 3, 221, 210).  The next points' loads as well take
+// registers that cost occupancy (128^3: 67.1).
+template <int V, int MM>
+struct ResidualIn {
+  float rr[2][V], dd[2][V], ri[2][MM][V];
+  __device__ __forceinline__ void load(const float* __restrict__ r_ref,
+                                       const float* __restrict__ dg,
+                                       const float* __restrict__ res_hist, size_t N, int nv,
+                                       int p, size_t n, unsigned mask) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int g = 2 * p + s;
+      if (g < nv) {
+        const size_t gn = (size_t)g * N + n;
+        ldv<V>(r_ref + gn, rr[s]);
+        ldv<V>(dg + gn, dd[s]);
+#pragma unroll
+        for (int i = 0; i < MM; ++i)
+          if (mask & (1u << i)) ldv<V>(res_hist + (size_t)i * nv * N + gn, ri[s][i]);
+      }
+    }
+  }
+  // R, stored in slot dest, and the Gram sums: the operations of residual_points
+  __device__ __forceinline__ void use(const float* hre, const float* him,
+                                      float* __restrict__ res_hist, size_t N, int nv, int p,
+                                      size_t n, int dest, unsigned mask, const GramW& gw,
+                                      double* acc) const {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int g = 2 * p + s;
+      if (g < nv) {
+        const double wg = (double)gw.w[g];
+        float R[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) R[v] = rr[s][v] + ((s ? him[v] : hre[v]) - dd[s][v]);
+        stv<V>(res_hist + (size_t)dest * nv * N + (size_t)g * N + n, R);
+        double sq = 0.0;
+#pragma unroll
+        for (int v = 0; v < V; ++v) sq += (double)R[v] * (double)R[v];
+        acc[MM] += sq;
+#pragma unroll
+        for (int i = 0; i < MM; ++i) {
+          if (i == dest) acc[i] += wg * sq;
+          if (mask & (1u << i)) {
+            double d = 0.0;
+#pragma unroll
+            for (int v = 0; v < V; ++v) d += (double)R[v] * (double)ri[s][i][v];
+            acc[i] += wg * d;
+          }
+        }
+      }
+    }
+  }
+};
+
 // The residual of V consecutive points n.. of pair p from the transformed
 // values h (hre/him in FP32, h64 in FP64), accumulated into the Gram partials
 // acc[0..MM-1] (slots; MM >= the history depth) and acc[MM] (the RMS sum).
@@ -389,6 +447,12 @@ __device__ inline void residual_points(const float* hre, const float* him, const
                                        float* __restrict__ dref, const float* __restrict__ dg,
                                        size_t N, int nv, int p, size_t n, int dest, unsigned mask,
                                        int kind, int order, const GramW& gw, double* acc) {
+  if constexpr (!ANCHOR && MM <= 5) {
+    ResidualIn<V, MM> in;
+    in.load(r_ref, dg, res_hist, N, nv, p, n, mask);
+    in.use(hre, him, res_hist, N, nv, p, n, dest, mask, gw, acc);
+    return;
+  }
   for (int s = 0; s < 2; ++s) {
     const int g = 2 * p + s;
     if (g >= nv) break;
@@ -510,7 +574,7 @@ __device__ inline void write_partials(const double* acc, int M, double* __restri
   }
 }
 
-template <bool ANCHOR, int V>
+template <bool ANCHOR, int V, int MM = kMaxDepth>
 __global__ __launch_bounds__(kRedThreads) void k_residual(
     const IterState* __restrict__ st, const void* __restrict__ spec, const float* __restrict__ w,
     float* __restrict__ tau_hist, float* __restrict__ res_hist, float* __restrict__ tau_ref,
@@ -518,12 +582,12 @@ __global__ __launch_bounds__(kRedThreads) void k_residual(
     const float* __restrict__ dg, size_t N, int nv, int npair, int M, int kind, int order,
     double* __restrict__ partials, GramW gw) {
   if (skip_iteration<ANCHOR>(st->done)) return;
-  __shared__ double red[(kMaxDepth + 1) * (kRedThreads / 64)];
+  __shared__ double red[(MM + 1) * (kRedThreads / 64)];
   const int dest = st->dest;
   const unsigned mask = other_slots(st, M, dest);
-  double acc[kMaxDepth + 1];
+  double acc[MM + 1];
 #pragma unroll
-  for (int i = 0; i <= kMaxDepth; ++i) acc[i] = 0.0;
+  for (int i = 0; i <= MM; ++i) acc[i] = 0.0;
   const size_t NQ = N / V;
   const size_t total = (size_t)npair * NQ;
   for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < total;
@@ -556,11 +620,11 @@ __global__ __launch_bounds__(kRedThreads) void k_residual(
         him[v] = pk[2 * v + 1];
       }
     }
-    residual_points<ANCHOR, V>(hre, him, h64, w, tau_hist, res_hist, tau_ref, tau_lo, r_ref, dref,
+    residual_points<ANCHOR, V, MM>(hre, him, h64, w, tau_hist, res_hist, tau_ref, tau_lo, r_ref, dref,
                                dg,
                                N, nv, p, n, dest, mask, kind, order, gw, acc);
   }
-  write_partials(acc, M, partials, red);
+  write_partials<MM>(acc, M, partials, red);
 }
 
 // One control step on a (shared-memory) copy of the state; single thread.

@@ -936,7 +936,13 @@ template <bool ANCHOR, int V>
 void launch_residual(const Layout& L, void* ws, const rism3d_opts* op, unsigned nblk,
                      hipStream_t s) {
   TIMED(ANCHOR ? F_RESIDUAL64 : F_RESIDUAL32, s);
-  hipLaunchKernelGGL((k_residual<ANCHOR, V>), dim3(nblk), dim3(kRedThreads), 0, s,
+  // as in the fused residual, the tightest bound of the depth: fewer sums a thread
+  auto k = &k_residual<ANCHOR, V, kMaxDepth>;
+  if constexpr (!ANCHOR) {
+    if (L.M <= 3) k = &k_residual<false, V, 3>;
+    else if (L.M <= 5) k = &k_residual<false, V, 5>;
+  }
+  hipLaunchKernelGGL(k, dim3(nblk), dim3(kRedThreads), 0, s,
                      at<IterState>(ws, L.off_state), at<void>(ws, L.off_spec),
                      at<float>(ws, L.off_w), at<float>(ws, L.off_tau), at<float>(ws, L.off_res),
                      at<float>(ws, L.off_tref), at<float>(ws, L.off_tlo), at<float>(ws, L.off_rref),

@@ -364,6 +364,26 @@ def test_single_site_64_golden(R):
     assert abs(sfe - ref["sfe_ref"]) <= SFE_RTOL * abs(ref["sfe_ref"])
 
 
+# History bounds of the residual kernel behind other x lengths (3, 5 and more
+# slots), rows of two-point and four-point vectors.
+@pytest.mark.parametrize("depth", [2, 3, 5, 6])
+@pytest.mark.parametrize("shape", [(20, 18, 50), (18, 24, 20)])
+def test_residual_history_bounds(R, O, depth, shape):
+    """The RMS after each iteration, until the history has turned over, follows the
+    oracle's; bar of the Anderson history above: the FP32 residual's 1e-5, ten
+    times amplified by the coefficients."""
+    prob = inputs.small_problem(8, n_atoms=8, shape=shape, radius=2.5, saline=True, closure="kh",
+                                charge_scale=1.0, mdiis_depth=depth)
+    print(f"history {shape} depth {depth}", flush=True)
+    s, chi, dk = _run(R, prob)
+    ref = O.solve(O.build_system(prob, chi, dk), tol=1e-6)
+    for k in range(1, depth + 3):
+        s.opts.max_iter = k
+        rms = s.solve(allow_noconv=True).rms
+        print(f"  iteration {k}: rms {rms:.6e} oracle {ref.rms_history[k - 1]:.6e}", flush=True)
+        assert abs(rms - ref.rms_history[k - 1]) <= 1e-4 * ref.rms_history[k - 1]
+
+
 @pytest.mark.parametrize("name", ["solute_200_saline", "warm_20000"])
 def test_full_size_golden(R, name):
     """The 128^3 workloads (200-atom solute in water + 0.1 M NaCl, and in
