@@ -601,7 +601,7 @@ void set_tune(const Layout& L, Tune t) {
   g_tunes.push_back({std::array<int, 4>{L.nx, L.ny, L.nz, L.nv}, t});
 }
 
-template <typename C, int N, int AXIS, int LINES = fixed_lines<C, N, AXIS>()>
+template <typename C, int N, int AXIS, int LINES>
 void launch_fixed_n(const Layout& L, C* spec, const C* tw, int forward, const int* done,
                     hipStream_t s, Batch bt = {}) {
   unsigned grid;
@@ -617,9 +617,21 @@ void launch_fixed_n(const Layout& L, C* spec, const C* tw, int forward, const in
                      spec, L.nx, L.ny, L.nz, L.npair, tw, forward, done, bt.stride);
 }
 
-// y pass of the FP32 iterations with a tuned width.  lines = 0: 16, a whole
-// 128-byte line of each row (5 sites at 128^3: 16.3 us, 32 lines 19.7, 8 lines
-// 26.9; 3 sites at 64^3 4.0, 4.2, 5.6; at 256^3 82, 103, 112).
+void launch_twiddles(const TwiddleAxes& ax, hipStream_t s) {
+  const int n = std::max(ax.n[0], std::max(ax.n[1], ax.n[2]));
+  hipLaunchKernelGGL(k_twiddles, dim3(blocks_for(2 * n, 256), 3), dim3(256), 0, s, ax);
+}
+
+// Lines per workgroup of the FP32 passes: 8 rows in x, and in y and z 16 columns,
+// a whole 128-byte line of each row.  x: one grid at 32^3 2.6 us, 128 rows 6.8 (8
+// workgroups in all); three at 128^3 17.7, 32 rows 21.2; at 256^3 127.8, 16 rows
+// 134.1.  y: one at 32^3 2.6, 32 columns 3.0; three at 128^3 16.2, 32 columns 19.6,
+// 8 columns 26.7; at 256^3 161.9, 8 columns 194.3.  512 points take 8 columns, with
+// two workgroups a CU (one at 512^3: 583, 16 columns 921).
+template <int N, int AXIS>
+constexpr int fixed32_lines() { return AXIS == 0 || N > 256 ? 8 : 16; }
+
+// y pass of the FP32 iterations with a tuned width (lines = 0: default).
 template <int N>
 void launch_y32_n(const Layout& L, float2* spec, const float2* tw, int forward, const int* done,
                   hipStream_t s, Batch bt, int lines) {
@@ -637,7 +649,9 @@ void launch_y32_n(const Layout& L, float2* spec, const float2* tw, int forward, 
         break;
       }
       [[fallthrough]];
-    default: launch_fixed_n<float2, N, 1, 16>(L, spec, tw, forward, done, s, bt); break;
+    default:
+      launch_fixed_n<float2, N, 1, fixed32_lines<N, 1>()>(L, spec, tw, forward, done, s, bt);
+      break;
   }
 }
 
@@ -656,17 +670,25 @@ bool launch_y32(const Layout& L, float2* spec, const float2* tw, int forward, co
   }
 }
 
+template <typename C, int N, int AXIS>
+void launch_fixed_default(const Layout& L, C* spec, const C* tw, int forward, const int* done,
+                          hipStream_t s, Batch bt) {
+  constexpr int lines = std::is_same<C, float2>::value ? fixed32_lines<N, AXIS>()
+                                                       : fixed_lines<C, N, AXIS>();
+  launch_fixed_n<C, N, AXIS, lines>(L, spec, tw, forward, done, s, bt);
+}
+
 template <typename C, int AXIS>
 bool launch_fixed_axis(int n, const Layout& L, C* spec, const C* tw, int forward, const int* done,
                        hipStream_t s, Batch bt) {
   switch (n) {
-    case 32: launch_fixed_n<C, 32, AXIS>(L, spec, tw, forward, done, s, bt); return true;
-    case 64: launch_fixed_n<C, 64, AXIS>(L, spec, tw, forward, done, s, bt); return true;
-    case 96: launch_fixed_n<C, 96, AXIS>(L, spec, tw, forward, done, s, bt); return true;
-    case 128: launch_fixed_n<C, 128, AXIS>(L, spec, tw, forward, done, s, bt); return true;
-    case 192: launch_fixed_n<C, 192, AXIS>(L, spec, tw, forward, done, s, bt); return true;
-    case 256: launch_fixed_n<C, 256, AXIS>(L, spec, tw, forward, done, s, bt); return true;
-    case 512: launch_fixed_n<C, 512, AXIS>(L, spec, tw, forward, done, s, bt); return true;
+    case 32: launch_fixed_default<C, 32, AXIS>(L, spec, tw, forward, done, s, bt); return true;
+    case 64: launch_fixed_default<C, 64, AXIS>(L, spec, tw, forward, done, s, bt); return true;
+    case 96: launch_fixed_default<C, 96, AXIS>(L, spec, tw, forward, done, s, bt); return true;
+    case 128: launch_fixed_default<C, 128, AXIS>(L, spec, tw, forward, done, s, bt); return true;
+    case 192: launch_fixed_default<C, 192, AXIS>(L, spec, tw, forward, done, s, bt); return true;
+    case 256: launch_fixed_default<C, 256, AXIS>(L, spec, tw, forward, done, s, bt); return true;
+    case 512: launch_fixed_default<C, 512, AXIS>(L, spec, tw, forward, done, s, bt); return true;
     default: return false;
   }
 }
@@ -1230,10 +1252,12 @@ rism3d_status prepare(const rism3d_problem* pr, const Layout& L, void* ws, hipSt
                      at<float>(ws, L.off_chi32), at<double>(ws, L.off_chi64),
                      at<double>(ws, L.off_q64));
   LAUNCH_CHECK();
-  const int dims[3] = {L.nx, L.ny, L.nz};
-  for (int a = 0; a < 3; ++a)
-    hipLaunchKernelGGL(k_twiddles, dim3(blocks_for(2 * dims[a], 256)), dim3(256), 0, s, dims[a],
-                       at<float2>(ws, L.off_tw32[a]), at<double2>(ws, L.off_tw64[a]));
+  TwiddleAxes ax{{L.nx, L.ny, L.nz}, {}, {}};
+  for (int a = 0; a < 3; ++a) {
+    ax.tw32[a] = at<float2>(ws, L.off_tw32[a]);
+    ax.tw64[a] = at<double2>(ws, L.off_tw64[a]);
+  }
+  launch_twiddles(ax, s);
   hipLaunchKernelGGL(k_mark_prepared, dim3(1), dim3(1), 0, s, at<IterState>(ws, L.off_state),
                      layout_key(L));
   LAUNCH_CHECK();
@@ -1478,13 +1502,10 @@ rism3d_status transform_on(int nx, int ny, int nz, int count, void* d_data, int 
   const size_t offs[3] = {0, align_up(2 * (size_t)nx * sizeof(float2)),
                           align_up(2 * (size_t)nx * sizeof(float2)) +
                               align_up(2 * (size_t)ny * sizeof(float2))};
-  const int dims[3] = {nx, ny, nz};
-  const float2* tw[3];
-  for (int a = 0; a < 3; ++a) {
-    hipLaunchKernelGGL(k_twiddles, dim3(blocks_for(2 * dims[a], 256)), dim3(256), 0, s, dims[a],
-                       at<float2>(ws, offs[a]), (double2*)nullptr);
-    tw[a] = at<float2>(ws, offs[a]);
-  }
+  TwiddleAxes ax{{nx, ny, nz}, {}, {}};
+  for (int a = 0; a < 3; ++a) ax.tw32[a] = at<float2>(ws, offs[a]);
+  launch_twiddles(ax, s);
+  const float2* const tw[3] = {ax.tw32[0], ax.tw32[1], ax.tw32[2]};
   launch_fft3_on(L, static_cast<float2*>(d_data), tw, forward, (const int*)nullptr, s);
   LAUNCH_CHECK();
   return RISM3D_OK;

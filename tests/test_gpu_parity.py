@@ -83,6 +83,15 @@ def test_transform_plans(R, shape, offset):
     assert np.abs(back - x).max() / np.abs(x).max() < 2e-6
 
 
+# Remainders of the tiles of the fixed lengths: 30 rows against 8, columns against
+# 16 and, at 512 points, 8.
+@pytest.mark.parametrize("shape", [(3, 5, 32), (3, 5, 96), (9, 32, 20), (64, 3, 18), (5, 256, 36),
+                                   (96, 3, 50), (2, 512, 12), (512, 2, 20), (3, 3, 512)])
+def test_transform_tile_remainders(R, shape):
+    """Bar as for the other transforms."""
+    test_transform_plans(R, shape, 0)
+
+
 @pytest.mark.parametrize("name", ["water", "saline", "single"])
 def test_potential_matches_oracle(R, O, name):
     if name == "single":
