@@ -70,37 +70,6 @@ __global__ void k_init_state(IterState* st, float eta, int warm) {
   st->hold = 0;
 }
 
-// Place the starting tau (the caller's, or zero) in history slot 0, where the
-// first update reads it; keeps the iteration kernels independent of the call.
-// The start: tau_ref = tau0 (or 0) and delta = 0 in the first slot.
-__global__ void k_init_tau(const float* __restrict__ tau0, float* __restrict__ slot0,
-                           float* __restrict__ tau_ref, float* __restrict__ tau_lo, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    slot0[i] = 0.0f;
-    tau_ref[i] = tau0 ? tau0[i] : 0.0f;
-    tau_lo[i] = 0.0f;
-  }
-}
-
-__global__ void k_mark_prepared(IterState* st, unsigned layout_key) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    st->prepared = kPreparedMagic;
-    st->layout_key = layout_key;
-    st->done = 1;
-    st->final_slot = -1;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Step 6 + step 2 fused: MDIIS update, in difference form about the newest
-// stored pair b (which keeps sum c_i = 1 exact in FP32):
-//   tau = tau_b + sum_i c_i (tau_i - tau_b) + eta sum_i c_i R_i,
-// stored in the destination slot (as delta = tau - tau_ref); then the closure.  ANCHOR: c_sr = g - 1 - tau
-// in FP64 (double2 grid).  Otherwise the FP32 increment dc = dg - delta about
-// the anchor, with dg kept for the residual.  Two sites share one complex grid
-// (site 2p real part, site 2p+1 imaginary part).
-// ---------------------------------------------------------------------------
 // V consecutive floats (V = 4: one 16-byte access, V = 2: one of 8 bytes).
 template <int V>
 __device__ inline void ldv(const float* __restrict__ p, float* o) {
@@ -127,6 +96,42 @@ __device__ inline void stv(float* __restrict__ p, const float* v) {
   }
 }
 
+// Place the starting tau (the caller's, or zero) in history slot 0, where the
+// first update reads it; keeps the iteration kernels independent of the call.
+// The start: tau_ref = tau0 (or 0) and delta = 0 in the first slot.
+// V floats a thread: 4 where the caller's tau0 is 16-byte aligned (n is a multiple
+// of 8), else 1 (31 and 25.5 us at 5 sites of 128^3).
+template <int V>
+__global__ void k_init_tau(const float* __restrict__ tau0, float* __restrict__ slot0,
+                           float* __restrict__ tau_ref, float* __restrict__ tau_lo, size_t n) {
+  const size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
+  if (i < n) {
+    float t[V] = {}, z[V] = {};
+    if (tau0) ldv<V>(tau0 + i, t);
+    stv<V>(slot0 + i, z);
+    stv<V>(tau_ref + i, t);
+    stv<V>(tau_lo + i, z);
+  }
+}
+
+__global__ void k_mark_prepared(IterState* st, unsigned layout_key) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) {
+    st->prepared = kPreparedMagic;
+    st->layout_key = layout_key;
+    st->done = 1;
+    st->final_slot = -1;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Step 6 + step 2 fused: MDIIS update, in difference form about the newest
+// stored pair b (which keeps sum c_i = 1 exact in FP32):
+//   tau = tau_b + sum_i c_i (tau_i - tau_b) + eta sum_i c_i R_i,
+// stored in the destination slot (as delta = tau - tau_ref); then the closure.  ANCHOR: c_sr = g - 1 - tau
+// in FP64 (double2 grid).  Otherwise the FP32 increment dc = dg - delta about
+// the anchor, with dg kept for the residual.  Two sites share one complex grid
+// (site 2p real part, site 2p+1 imaginary part).
+// ---------------------------------------------------------------------------
 // Per-workgroup copy of what the update needs from the state.
 struct UpdateCtl {
   float cf[kMaxDepth];
@@ -1024,33 +1029,45 @@ __global__ __launch_bounds__(kElemThreads) void k_output(
 }
 
 // ---------------------------------------------------------------------------
-// Eq 17 / 18 / PSE-n free-energy density, summed per site in FP64.
+// Eq 17 / 18 / PSE-n free-energy density of site blockIdx.y, summed in FP64.
 //   h = g - 1,  c = g - 1 - t = g - 1 - tau - f,  d = -w + tau
+// Bound by memory (five FP32 fields): four points a thread as 16-byte loads (every
+// grid has a multiple of 8 points), the sites in parallel.  KH, 5 sites at 128^3:
+// 67 us with a point a load and one site after the other, 44.5 now.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kRedThreads) void k_sfe_partial(
     const IterState* __restrict__ st, const float* __restrict__ tau_hist,
     const float* __restrict__ tau_ref, const float* __restrict__ tau_lo,
     const float* __restrict__ w, const float* __restrict__ phi_lr, size_t N, int nv, int kind,
     int order, SiteConsts sc, double* __restrict__ partials) {
-  // partials[block][2 nv]: the free-energy density sums, then the sums of c
+  // partials[2 nv][block]: the free-energy density sums, then the sums of c
   __shared__ double red[kRedThreads / 64];
   const int slot = st->final_slot;
   if (slot < 0) return;
   double inv_fact = 1.0;
   for (int i = 2; i <= order + 1; ++i) inv_fact /= (double)i;
-  for (int g = 0; g < nv; ++g) {
-    double acc = 0.0, acc_c = 0.0;
-    const float* tau = tau_hist + ((size_t)slot * nv + g) * N;
-    const float* tr = tau_ref + (size_t)g * N;
-    const float* tl = tau_lo + (size_t)g * N;
-    const float* wg = w + (size_t)g * N;
-    for (size_t n = (size_t)blockIdx.x * blockDim.x + threadIdx.x; n < N;
-         n += (size_t)gridDim.x * blockDim.x) {
-      const double t = ((double)tr[n] + (double)tl[n]) + (double)tau[n];
-      const double d = -(double)wg[n] + t;
+  const int g = blockIdx.y;
+  const double coul = (double)sc.coul[g];
+  const float* tau = tau_hist + ((size_t)slot * nv + g) * N;
+  const float* tr = tau_ref + (size_t)g * N;
+  const float* tl = tau_lo + (size_t)g * N;
+  const float* wg = w + (size_t)g * N;
+  double acc = 0.0, acc_c = 0.0;
+  for (size_t n = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; n < N;
+       n += (size_t)gridDim.x * blockDim.x * 4) {
+    float t4[4], r4[4], l4[4], w4[4], p4[4];
+    ldv<4>(tau + n, t4);
+    ldv<4>(tr + n, r4);
+    ldv<4>(tl + n, l4);
+    ldv<4>(wg + n, w4);
+    ldv<4>(phi_lr + n, p4);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const double t = ((double)r4[v] + (double)l4[v]) + (double)t4[v];
+      const double d = -(double)w4[v] + t;
       const double gg = closure_g(d, kind, order);
       const double h = gg - 1.0;
-      const double c = h - t - (double)sc.coul[g] * (double)phi_lr[n];
+      const double c = h - t - coul * (double)p4[v];
       double phi = -c - 0.5 * h * c;
       if (kind == RISM3D_HNC) phi += 0.5 * h * h;
       else if (kind == RISM3D_KH) phi += (h < 0.0) ? 0.5 * h * h : 0.0;
@@ -1058,38 +1075,42 @@ __global__ __launch_bounds__(kRedThreads) void k_sfe_partial(
       acc += phi;
       acc_c += c;
     }
-    const double s = block_sum(acc, red);
-    const double sc_sum = block_sum(acc_c, red);
-    if (threadIdx.x == 0) {
-      partials[(size_t)blockIdx.x * 2 * nv + g] = s;
-      partials[(size_t)blockIdx.x * 2 * nv + nv + g] = sc_sum;
-    }
+  }
+  const double s = block_sum(acc, red);
+  const double sc_sum = block_sum(acc_c, red);
+  if (threadIdx.x == 0) {
+    partials[(size_t)g * gridDim.x + blockIdx.x] = s;
+    partials[(size_t)(nv + g) * gridDim.x + blockIdx.x] = sc_sum;
   }
 }
 
 // out[g] = k_B T rho_g dV sum Phi_g (Eq 17/18), out[kMaxSites] their total,
-// out[kMaxSites + 1 + g] = rho_g dV sum c_g (the integral of Eq 19).
-__global__ __launch_bounds__(kRedThreads) void k_sfe_reduce(const double* __restrict__ partials,
-                                                            int nblocks, int nv, double scale,
-                                                            double dv, SiteConsts sc,
-                                                            double* __restrict__ out) {
-  __shared__ double red[kRedThreads / 64];
-  double total = 0.0;
-  for (int g = 0; g < nv; ++g) {
-    double v = 0.0, vc = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
-      v += partials[(size_t)b * 2 * nv + g];
-      vc += partials[(size_t)b * 2 * nv + nv + g];
-    }
-    const double s = block_sum(v, red);
-    const double s_c = block_sum(vc, red);
-    if (threadIdx.x == 0) {
-      out[g] = s * sc.rho[g] * scale;
-      out[kMaxSites + 1 + g] = s_c * sc.rho[g] * dv;
-      total += out[g];
+// out[kMaxSites + 1 + g] = rho_g dV sum c_g (the integral of Eq 19).  A wavefront
+// per quantity: a latency chain of 16 loads and 6 shuffles (one quantity after the
+// other by one workgroup took 11.8 us, now 5.9).
+constexpr int kSfeReduceThreads = 64 * 2 * kMaxSites;
+
+__global__ __launch_bounds__(kSfeReduceThreads) void k_sfe_reduce(
+    const double* __restrict__ partials, int nblocks, int nv, double scale, double dv,
+    SiteConsts sc, double* __restrict__ out) {
+  __shared__ double site[kMaxSites];
+  const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (q < 2 * nv) {
+    double v = 0.0;
+#pragma unroll 8
+    for (int b = lane; b < nblocks; b += 64) v += partials[(size_t)q * nblocks + b];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    if (lane == 0) {
+      if (q < nv) out[q] = site[q] = v * sc.rho[q] * scale;
+      else out[kMaxSites + 1 + q - nv] = v * sc.rho[q - nv] * dv;
     }
   }
-  if (threadIdx.x == 0) out[kMaxSites] = total;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double total = 0.0;
+    for (int g = 0; g < nv; ++g) total += site[g];
+    out[kMaxSites] = total;
+  }
 }
 
 // Copy of one history slot (the residual of a single map evaluation).
@@ -1098,13 +1119,19 @@ __global__ void k_copy_floats(const float* __restrict__ src, float* __restrict__
   if (i < n) dst[i] = src[i];
 }
 
-// The history slot of the accepted iterate (final_slot) of n = nv N floats.
+// The history slot of the accepted iterate (final_slot) of n = nv N floats; V as in
+// k_init_tau, by the alignment of dst (25.4 and 16.7 us at 5 sites of 128^3).
+template <int V>
 __global__ void k_copy_final_slot(const IterState* __restrict__ st,
                                   const float* __restrict__ hist, float* __restrict__ dst,
                                   size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
   const int slot = st->final_slot;
-  if (i < n && slot >= 0) dst[i] = hist[(size_t)slot * n + i];
+  if (i < n && slot >= 0) {
+    float v[V];
+    ldv<V>(hist + (size_t)slot * n + i, v);
+    stv<V>(dst + i, v);
+  }
 }
 
 // The next evaluation re-evaluates the iterate of a solved workspace (the

@@ -1264,23 +1264,44 @@ rism3d_status prepare(const rism3d_problem* pr, const Layout& L, void* ws, hipSt
   return RISM3D_OK;
 }
 
+bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+
+// The starting tau (null: zero) as the reference, with a zero increment.
+void launch_init_tau(const Layout& L, void* ws, const float* tau0, hipStream_t s) {
+  const size_t n = (size_t)L.nv * L.N;
+  const int v = aligned16(tau0) ? 4 : 1;
+  hipLaunchKernelGGL((v == 4 ? &k_init_tau<4> : &k_init_tau<1>),
+                     dim3(blocks_for(n / v, kElemThreads)), dim3(kElemThreads), 0, s, tau0,
+                     at<float>(ws, L.off_tau), at<float>(ws, L.off_tref),
+                     at<float>(ws, L.off_tlo), n);
+}
+
+// The residual of the accepted iterate.
+void launch_copy_residual(const Layout& L, void* ws, float* dst, hipStream_t s) {
+  const size_t n = (size_t)L.nv * L.N;
+  const int v = aligned16(dst) ? 4 : 1;
+  hipLaunchKernelGGL((v == 4 ? &k_copy_final_slot<4> : &k_copy_final_slot<1>),
+                     dim3(blocks_for(n / v, kElemThreads)), dim3(kElemThreads), 0, s,
+                     at<IterState>(ws, L.off_state), at<float>(ws, L.off_res), dst, n);
+}
+
 // Launches the SFE density sums of a solved workspace into its output slot
 // (read back with read_sfe after the stream synchronises).
 void launch_sfe(const rism3d_problem* pr, const rism3d_opts* op, const Layout& L, void* ws,
                 hipStream_t s) {
   const SiteConsts sc = site_consts(pr, L.beta);
-  unsigned nblk = blocks_for(L.N, kRedThreads);
+  unsigned nblk = blocks_for(L.N / 4, kRedThreads);
   if (nblk > (unsigned)kRedBlocks) nblk = kRedBlocks;
   {
     TIMED(F_SFE, s);
-    hipLaunchKernelGGL(k_sfe_partial, dim3(nblk), dim3(kRedThreads), 0, s,
+    hipLaunchKernelGGL(k_sfe_partial, dim3(nblk, L.nv), dim3(kRedThreads), 0, s,
                        at<IterState>(ws, L.off_state), at<float>(ws, L.off_tau),
                        at<float>(ws, L.off_tref), at<float>(ws, L.off_tlo), at<float>(ws, L.off_w),
                        at<float>(ws, L.off_phi), L.N, L.nv,
                        (int)op->closure, order_of(op), sc, at<double>(ws, L.off_part));
   }
   const double scale = L.dv / L.beta;   // k_B T dV
-  hipLaunchKernelGGL(k_sfe_reduce, dim3(1), dim3(kRedThreads), 0, s, at<double>(ws, L.off_part),
+  hipLaunchKernelGGL(k_sfe_reduce, dim3(1), dim3(kSfeReduceThreads), 0, s, at<double>(ws, L.off_part),
                      (int)nblk, L.nv, scale, L.dv, sc, at<double>(ws, L.off_out));
 }
 
@@ -1582,10 +1603,7 @@ rism3d_status rism3d_solve(const rism3d_problem* pr, const rism3d_opts* op, cons
   const float* t0 = attempt == 0 ? tau0 : nullptr;
   hipLaunchKernelGGL(k_init_state, dim3(1), dim3(1), 0, s, dst, (float)op->mdiis_eta,
                      t0 ? 1 : 0);
-  hipLaunchKernelGGL(k_init_tau, dim3(blocks_for((size_t)L.nv * L.N, kElemThreads)),
-                     dim3(kElemThreads), 0, s, t0, at<float>(ws, L.off_tau),
-                     at<float>(ws, L.off_tref), at<float>(ws, L.off_tlo),
-                     (size_t)L.nv * L.N);
+  launch_init_tau(L, ws, t0, s);
   LAUNCH_CHECK();
   const int every = op->anchor_every > 0 ? op->anchor_every : kDefaultAnchorEvery;
   // One anchor period (an FP64 anchor evaluation + every-1 FP32 increments) is
@@ -1819,10 +1837,7 @@ rism3d_status rism3d_solve_batch(int n, const rism3d_problem* prs, const rism3d_
       const float* t0 = tau0 ? tau0[i] : nullptr;
       hipLaunchKernelGGL(k_init_state, dim3(1), dim3(1), 0, s, at<IterState>(w, L.off_state),
                          (float)op->mdiis_eta, t0 ? 1 : 0);
-      hipLaunchKernelGGL(k_init_tau, dim3(blocks_for((size_t)L.nv * L.N, kElemThreads)),
-                         dim3(kElemThreads), 0, s, t0, at<float>(w, L.off_tau),
-                         at<float>(w, L.off_tref), at<float>(w, L.off_tlo),
-                         (size_t)L.nv * L.N);
+      launch_init_tau(L, w, t0, s);
       LAUNCH_CHECK();
     }
   const int every = op->anchor_every > 0 ? op->anchor_every : kDefaultAnchorEvery;
@@ -2013,10 +2028,7 @@ rism3d_status rism3d_map(const rism3d_problem* pr, const rism3d_opts* op, const 
   one.tol = 0.0;   // never "converged": the single evaluation always runs to the end
   if (d_tau) {
     hipLaunchKernelGGL(k_init_state, dim3(1), dim3(1), 0, s, dst, (float)op->mdiis_eta, 1);
-    hipLaunchKernelGGL(k_init_tau, dim3(blocks_for((size_t)L.nv * L.N, kElemThreads)),
-                       dim3(kElemThreads), 0, s, d_tau, at<float>(ws, L.off_tau),
-                       at<float>(ws, L.off_tref), at<float>(ws, L.off_tlo),
-                       (size_t)L.nv * L.N);
+    launch_init_tau(L, ws, d_tau, s);
   } else {
     // the held iterate; its evaluation re-bases the reference on that same
     // iterate, so the solution stays in place for rism3d_thermo and the outputs
@@ -2024,8 +2036,7 @@ rism3d_status rism3d_map(const rism3d_problem* pr, const rism3d_opts* op, const 
   }
   launch_iteration(L, ws, &one, (1.0 / pr->dk), true, s);
   const size_t n = (size_t)L.nv * L.N;
-  hipLaunchKernelGGL(k_copy_final_slot, dim3(blocks_for(n, kElemThreads)), dim3(kElemThreads), 0,
-                     s, dst, at<float>(ws, L.off_res), d_res, n);
+  launch_copy_residual(L, ws, d_res, s);
   LAUNCH_CHECK();
   HIP_TRY(hipMemcpyAsync(&host, dst, sizeof(IterState), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
@@ -2053,15 +2064,12 @@ rism3d_status rism3d_map_increment(const rism3d_problem* pr, const rism3d_opts* 
   const size_t n = (size_t)L.nv * L.N;
   const double inv_dkt = 1.0 / pr->dk;
   hipLaunchKernelGGL(k_init_state, dim3(1), dim3(1), 0, s, dst, (float)op->mdiis_eta, 1);
-  hipLaunchKernelGGL(k_init_tau, dim3(blocks_for(n, kElemThreads)), dim3(kElemThreads), 0, s,
-                     d_tau_ref, at<float>(ws, L.off_tau), at<float>(ws, L.off_tref),
-                     at<float>(ws, L.off_tlo), n);
+  launch_init_tau(L, ws, d_tau_ref, s);
   launch_iteration(L, ws, &two, inv_dkt, true, s);    // FP64: R_ref at tau_ref
   hipLaunchKernelGGL(k_set_increment, dim3(blocks_for(n, kElemThreads)), dim3(kElemThreads), 0, s,
                      dst, at<float>(ws, L.off_tau), d_delta, n);
   launch_iteration(L, ws, &two, inv_dkt, false, s);   // FP32: R_ref + dh - dg
-  hipLaunchKernelGGL(k_copy_final_slot, dim3(blocks_for(n, kElemThreads)), dim3(kElemThreads), 0,
-                     s, dst, at<float>(ws, L.off_res), d_res, n);
+  launch_copy_residual(L, ws, d_res, s);
   LAUNCH_CHECK();
   HIP_TRY(hipMemcpyAsync(&host, dst, sizeof(IterState), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));

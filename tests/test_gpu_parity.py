@@ -204,6 +204,19 @@ def test_maps_at_flexible_lengths(R, O, saline, shape, closure):
     assert np.abs(res - ref).max() < 2e-6 * max(1.0, np.abs(ref).max())
 
 
+def test_map_of_unaligned_tau(R, O):
+    """A tau at 4 bytes past a 16-byte boundary takes the start's one-float copies:
+    the same values reach the same kernels, so the residual has the same bits."""
+    prob, s, sys_ = _map_case(R, O, True, (18, 20, 24), "kh")
+    rng = np.random.default_rng(29)
+    tau = torch.tensor(0.05 * rng.standard_normal(sys_.f.shape), dtype=torch.float32, device="cuda")
+    flat = torch.zeros(tau.numel() + 1, device="cuda")
+    shifted = flat[1:].view(tau.shape)
+    shifted.copy_(tau)
+    assert shifted.data_ptr() % 16 == 4
+    assert torch.equal(s.map(shifted)[0], s.map(tau)[0])
+
+
 # Remainders of the default tiles on fixed lengths: 180 x rows against 8, y lines
 # against 16, z columns against 8 (3 sites) and 4 (5 sites).
 @pytest.mark.parametrize("saline,shape", [(True, (10, 6, 64)), (True, (6, 10, 32)),
