@@ -368,6 +368,38 @@ __global__ __launch_bounds__(kElemThreads) void k_contract(
 // <R, R_i> for every other stored slot and <R, R> are accumulated in FP64;
 // per-block partial sums are written in block order (reduced by k_control).
 // ---------------------------------------------------------------------------
+// Lane 0: the sum over the wavefront, adding the pairs that shuffles by 32, 16, .., 1
+// lanes would (the same bits), without their trips through LDS.
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+__device__ __forceinline__ double wave_sum_lane0(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  // lane i < 32 of the two results: the values of lanes i and i + 32
+  v = __longlong_as_double(((long long)h[0] << 32) | l[0]) +
+      __longlong_as_double(((long long)h[1] << 32) | l[1]);
+  const long long c = __double_as_longlong(v);
+  const unsigned lo2 = (unsigned)c, hi2 = (unsigned)(c >> 32);
+  const auto l2 = __builtin_amdgcn_permlane16_swap(lo2, lo2, false, false);
+  const auto h2 = __builtin_amdgcn_permlane16_swap(hi2, hi2, false, false);
+  // lane i < 16: lanes i and i + 16
+  v = __longlong_as_double(((long long)h2[0] << 32) | l2[0]) +
+      __longlong_as_double(((long long)h2[1] << 32) | l2[1]);
+  v += dpp_d<0x108>(v);   // row_shl: lane i reads lane i + 8 of its row of 16, ...
+  v += dpp_d<0x104>(v);
+  v += dpp_d<0x102>(v);
+  v += dpp_d<0x101>(v);
+  return v;
+}
+
 __device__ inline double block_sum(double v, double* lds) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
   const int lane = threadIdx.x & 63;
@@ -384,8 +416,8 @@ __device__ inline double block_sum(double v, double* lds) {
 
 // What the FP32 residual of V consecutive points of a pair reads besides the
 // transform.  Bound by memory: both sites' loads are in flight before the first is
-// used (site after site: 3 sites at 64^3 13.9 us, now 13.4; 5 sites at 128^3 63.8,
-// 61.2; 3 sites at 256^3, depth 3, 221, 210).  The next points' loads as well take
+// used (site after site: 3 sites at 64^3 13.9 us, now 13.4, and 12.2 with the wave
+// sums below; 5 sites at 128^3 63.8, 61.2; 3 sites at 256^3, depth 3, 221, 210).  The next points' loads as well take
 // registers that cost occupancy (128^3: 67.1).
 template <int V, int MM>
 struct ResidualIn {
@@ -565,8 +597,7 @@ __device__ inline void write_partials(const double* acc, int M, double* __restri
 #pragma unroll
   for (int i = 0; i <= MM; ++i) {
     if (i < M || i == MM) {   // M is uniform: every thread takes the same branches
-      double v = acc[i];
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+      const double v = wave_sum_lane0(acc[i]);
       if (lane == 0) red[(i < M ? i : M) * nw + wv] = v;
     }
   }
@@ -744,10 +775,12 @@ __device__ void control_step(ControlScratch& cs, const double* sums, int M, doub
       st.stored[dest] = 0;
       int best = -1;
       double best_rms = 0.0;
-      for (int i = 0; i < M; ++i) {
-        if (st.stored[i] && (best < 0 || st.rms_slot[i] < best_rms)) {
+#pragma unroll
+      for (int i = 0; i < MM; ++i) {   // unrolled: the LDS reads do not wait for each other
+        const double r = st.rms_slot[i];
+        if (i < M && st.stored[i] && (best < 0 || r < best_rms)) {
           best = i;
-          best_rms = st.rms_slot[i];
+          best_rms = r;
         }
       }
       if (!anderson && best >= 0 && rms > 10.0 * best_rms) {
@@ -759,16 +792,19 @@ __device__ void control_step(ControlScratch& cs, const double* sums, int M, doub
         st.newest = dest;
         st.rms_slot[dest] = rms;
         st.stamp[dest] = ++st.stamp_counter;
-        for (int i = 0; i < M; ++i) {
-          if (st.stored[i] && i != dest) {
-            st.gram[dest][i] = sums[i];
-            st.gram[i][dest] = sums[i];
+#pragma unroll
+        for (int i = 0; i < MM; ++i) {
+          const double g = sums[i];
+          if (i < M && st.stored[i] && i != dest) {
+            st.gram[dest][i] = g;
+            st.gram[i][dest] = g;
           }
         }
         st.gram[dest][dest] = anderson ? sums[dest] : rr;   // weighted for Anderson (Eq 38)
       }
       int m = 0;
-      for (int i = 0; i < M; ++i) m += st.stored[i] != 0;
+#pragma unroll
+      for (int i = 0; i < MM; ++i) m += i < M && st.stored[i] != 0;
       cs.m = m;
       cs.mode = (!anderson && m > 1) ? kCtlSolve : kCtlDirect;
     }
@@ -899,8 +935,12 @@ __device__ void control_step(ControlScratch& cs, const double* sums, int M, doub
       c[0] = 1.0;
       st.restarts += 1;
     }
-    for (int i = 0; i < M; ++i) st.coef[i] = 0.0f;
-    for (int i = 0; i < mm; ++i) st.coef[slot[i]] = (float)c[i];
+#pragma unroll
+    for (int i = 0; i < MM; ++i)
+      if (i < M) st.coef[i] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < MM; ++i)
+      if (i < mm) st.coef[slot[i]] = (float)c[i];
     float eta = eta_static;
     if (eta_dynamic && !anderson) eta = (float)fmin(fmax(-0.2 * log(cs.rms), 0.1), 1.0);
     st.eta = eta;
@@ -923,6 +963,9 @@ __device__ void control_step(ControlScratch& cs, const double* sums, int M, doub
 // Reduce the partials of `nblocks` blocks in fixed order and run one control
 // step on the state (anchor: the evaluation was the FP64 one); all threads of
 // the calling workgroup participate.
+// Bound by one workgroup's latency: wave sums without LDS, idle wavefronts left
+// out and unrolled state scans took it from 11.2 to 8.8 us at 128 workgroups (64^3)
+// and from 13.9 to 10.1 at 1536 (5 sites at 128^3).
 // MM bounds the history depth (M <= MM): each thread holds MM + 1 sums.
 template <int MM = kMaxDepth>
 __device__ __forceinline__ void control_block(IterState* __restrict__ st_g,
@@ -939,43 +982,52 @@ __device__ __forceinline__ void control_block(IterState* __restrict__ st_g,
   // Each thread sums its strided workgroups b = t, t + T, ... for every
   // quantity (quantity q is the contiguous run partials[q * nblocks + b]).
   // The loads of U workgroups and all quantities are issued before any
-  // addition and without branches (quantities past M re-read quantity M,
-  // workgroups past the end re-read the last one; both add zero), so the
-  // round trip to rows just written by other CUs is paid once per U
-  // workgroups.  Then one LDS pass combines the per-wave sums in fixed order.
+  // addition (quantities past M re-read quantity M, workgroups past the end
+  // re-read the last one; both add zero), so the round trip to rows just
+  // written by other CUs is paid once per U workgroups; wavefronts without a
+  // workgroup of their own load nothing.  Then one LDS pass combines the
+  // per-wave sums in fixed order.
   constexpr int U = MM <= 5 ? 6 : 2;
+  constexpr int T = kCtlThreads;
   double v[MM + 1];
 #pragma unroll
   for (int q = 0; q <= MM; ++q) v[q] = 0.0;
-  const int T = (int)blockDim.x;
-  for (int b = threadIdx.x; b < nblocks; b += U * T) {
+  const int b0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x);   // the wave's first
+  const int lane = threadIdx.x & 63;
+  for (int bw = b0; bw < nblocks; bw += U * T) {
     double r[U][MM + 1];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int bb = b + u * T;
-      const size_t bc = (size_t)(bb < nblocks ? bb : nblocks - 1);
+      if (bw + u * T < nblocks) {
+        const int bb = bw + lane + u * T;
+        const size_t bc = (size_t)(bb < nblocks ? bb : nblocks - 1);
 #pragma unroll
-      for (int q = 0; q <= MM; ++q)
-        r[u][q] = partials[(size_t)(q <= M ? q : M) * (size_t)nblocks + bc];
+        for (int q = 0; q <= MM; ++q)
+          r[u][q] = partials[(size_t)(q <= M ? q : M) * (size_t)nblocks + bc];
+      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool in = b + u * T < nblocks;
+      if (bw + u * T < nblocks) {
+        const bool in = bw + lane + u * T < nblocks;
 #pragma unroll
-      for (int q = 0; q <= MM; ++q) v[q] += (in && q <= M) ? r[u][q] : 0.0;
+        for (int q = 0; q <= MM; ++q) v[q] += (in && q <= M) ? r[u][q] : 0.0;
+      }
     }
   }
 #pragma unroll
   for (int q = 0; q <= MM; ++q) {
     if (q <= M) {
-      for (int off = 32; off > 0; off >>= 1) v[q] += __shfl_down(v[q], off, 64);
-      if ((threadIdx.x & 63) == 0) cs.wsum[threadIdx.x >> 6][q] = v[q];
+      double w = 0.0;
+      if (b0 < nblocks) w = wave_sum_lane0(v[q]);
+      if (lane == 0) cs.wsum[threadIdx.x >> 6][q] = w;
     }
   }
   __syncthreads();
   if (threadIdx.x <= M) {
     double t = 0.0;
-    for (int wv = 0; wv < (int)(blockDim.x >> 6); ++wv) t += cs.wsum[wv][threadIdx.x];
+#pragma unroll
+    for (int wv = 0; wv < T / 64; ++wv) t += cs.wsum[wv][threadIdx.x];
     cs.sums[threadIdx.x] = t;
   }
   __syncthreads();
