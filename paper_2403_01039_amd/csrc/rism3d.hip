@@ -507,8 +507,8 @@ void launch_potential_k(const Layout& L, void* ws, double dr, const SiteConsts& 
 }
 
 // Four points a thread from 2^20 points on (rows of a multiple of four): 5
-// sites, 200 atoms at 128^3 611 us against 656 with two.  Smaller grids need the
-// threads: 96^3 329 with four, 304 with two; 64^3 132 and 102.
+// sites, 200 atoms at 128^3 642 us against 689 with two.  Smaller grids need the
+// threads: 96^3 364 with four, 347 with two; 64^3 157 and 123.
 template <int NV>
 void launch_potential_nv(const Layout& L, void* ws, double dr, const SiteConsts& sc,
                          hipStream_t s) {

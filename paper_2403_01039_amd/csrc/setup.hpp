@@ -86,8 +86,8 @@ struct ExpNeg {
 // latency.  1/dc and dc come from one reciprocal square root, e^{-d} from
 // ExpNeg; beyond 38 A it adds below FP64 resolution and is taken as 0 (and not
 // evaluated where no point of the wave is nearer).  128^3, 200 atoms, 5 sites: 1439 us with a square root,
-// two divisions and the library's exp at one point a thread, 611 us now (45 FP64
-// operations a pair, 0.79 of the FP64 issue rate).
+// two divisions and the library's exp at one point a thread, 642 us now (45 FP64
+// operations a pair, 0.75 of the FP64 issue rate).
 template <int NV, int K>
 __global__ __launch_bounds__(kPotThreads) void k_potential(
     const double4* __restrict__ atoms, const double2* __restrict__ lj, int n_atoms, int nx, int ny,
