@@ -284,8 +284,10 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_fixed(
   const int total = nl * N;
   // FP32 y/z tiles of full width move neighbouring lines (x, x+1) as one
   // 16-byte vector: half the memory instructions, no runtime index division.
+  // An odd nx puts every other row, and data that is only 8-byte aligned every
+  // row, off the 16-byte boundary: those move line by line.
   constexpr bool kVec = std::is_same<C, float2>::value && AXIS != 0 && LINES % 2 == 0;
-  const bool vec = kVec && nl == LINES;
+  const bool vec = kVec && nl == LINES && nx % 2 == 0 && ((uintptr_t)data & 15) == 0;
   if constexpr (kVec) {
     if (vec) {
       constexpr int H = LINES / 2;

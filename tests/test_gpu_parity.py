@@ -92,6 +92,17 @@ def test_transform_tile_remainders(R, shape):
     test_transform_plans(R, shape, 0)
 
 
+# Whole tiles of the lengths with fixed kernels (y or z of 32 to 512 points) whose
+# rows are not 16-byte aligned: odd nx of at least one tile (16 columns, 8 at 512
+# points), and data that is 8-byte but not 16-byte aligned.
+@pytest.mark.parametrize("shape,offset", [((3, 32, 25), 0), ((32, 3, 45), 0), ((64, 96, 27), 0),
+                                          ((2, 512, 9), 0), ((32, 32, 18), 1), ((128, 2, 32), 1),
+                                          ((2, 256, 16), 1)])
+def test_transform_unaligned_rows(R, shape, offset):
+    """Bar as for the other transforms."""
+    test_transform_plans(R, shape, offset)
+
+
 @pytest.mark.parametrize("name", ["water", "saline", "single"])
 def test_potential_matches_oracle(R, O, name):
     if name == "single":
