@@ -18,6 +18,7 @@ constexpr double kDMin = 0.01;               // A, distance clamp in Eq 22
 constexpr double kBetaUCap = 1.0e4;          // cap on beta*u before f is removed
 static_assert(kScreen == 1.0, "the potential kernel evaluates (1 - e^{-d/l})/d with l = 1 A");
 
+constexpr double kFarAway = 0x1p511;   // stands for an infinite coordinate (k_prep_atoms)
 constexpr int kMaxSites = RISM3D_MAX_SITES;
 constexpr int kMaxDepth = RISM3D_MAX_DEPTH;
 constexpr int kHistLen = RISM3D_HISTORY_LEN;

@@ -136,12 +136,13 @@ __global__ __launch_bounds__(kGradThreads) void k_sfe_grad(
     __syncthreads();
     if (wave == 0 && sub == 0 && atom < n_atoms) {
       double* o = out + ((size_t)blockIdx.x * n_atoms + atom) * 3;
+      const double pos[3] = {at[i].x, at[i].y, at[i].z};
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         double v = 0.0;
         for (int w = 0; w < kGradThreads / 64; ++w)
           for (int k = 0; k < subs; ++k) v += s_red[w][k * lanes + al][c];
-        o[c] = v * scale;
+        o[c] = fabs(pos[c]) < kFarAway ? v * scale : __longlong_as_double(0x7ff8000000000000);
       }
     }
   }

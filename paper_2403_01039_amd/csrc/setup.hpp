@@ -16,9 +16,19 @@ __device__ __forceinline__ void store_k(float* __restrict__ p, const float* v) {
   else *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
 }
 
+// A coordinate within 2^510, so that squared distances stay finite and 1/d^3 is 0
+// (kFarAway: an infinite one); NaN stays NaN.
+__device__ __forceinline__ double in_range(double x) {
+  const double most = isinf(x) ? kFarAway : 0.5 * kFarAway;
+  return fabs(x) > most || isinf(x) ? copysign(most, x) : x;
+}
+
 // Solute atoms relative to the grid corner r0 (with the charge in .w), and per
 // (atom, site) LJ coefficients beta*4*eps*sigma^12 and beta*4*eps*sigma^6
-// (Lorentz-Berthelot mixing).
+// (Lorentz-Berthelot mixing).  The pair loops clamp distances with maxima, which
+// take the other operand for a NaN, and form 1/d by steps that need d^2 finite:
+// so a NaN coordinate is carried by the charge and the coefficients, and far
+// coordinates are brought into range here, once an atom.
 __global__ void k_prep_atoms(const double* __restrict__ xyz, const double* __restrict__ q,
                              const double* __restrict__ sigma, const double* __restrict__ eps,
                              int n_atoms, double r0x, double r0y, double r0z, double beta,
@@ -26,11 +36,14 @@ __global__ void k_prep_atoms(const double* __restrict__ xyz, const double* __res
                              double2* __restrict__ lj) {
   const int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= n_atoms) return;
-  atoms[a] = make_double4(xyz[3 * a] - r0x, xyz[3 * a + 1] - r0y, xyz[3 * a + 2] - r0z, q[a]);
+  const double x = in_range(xyz[3 * a] - r0x), y = in_range(xyz[3 * a + 1] - r0y),
+               z = in_range(xyz[3 * a + 2] - r0z);
+  const double nan = isnan(x) || isnan(y) || isnan(z) ? x + y + z : 0.0;
+  atoms[a] = make_double4(x, y, z, q[a] + nan);
   for (int g = 0; g < nv; ++g) {
     const double s = 0.5 * (sigma[a] + sites.sigma[g]);
     const double e = sqrt(eps[a] * sites.eps[g]);
-    const double s6 = s * s * s * s * s * s;
+    const double s6 = s * s * s * s * s * s + nan;
     lj[(size_t)a * nv + g] = make_double2(beta * 4.0 * e * s6 * s6, beta * 4.0 * e * s6);
   }
 }

@@ -81,6 +81,28 @@ def test_atom_on_a_grid_point(R, O):
     assert np.abs(got - ref).max() <= 1e-10 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("n_atoms", [5, 70])
+def test_atom_out_of_range(R, n_atoms):
+    """A NaN coordinate makes that atom's gradient NaN; at an infinite coordinate
+    the pair force is 0 times infinity along it; where the squared distance
+    overflows the gradient is 0.  The other atoms' gradients keep their bits."""
+    prob = inputs.small_problem(56, n_atoms=n_atoms, shape=(16, 18, 20), radius=5.0)
+    g = torch.tensor(inputs.synthetic_distribution(prob, 56, exclusion=1.0), device="cuda")
+    ref = _solver(R, prob)[0].sfe_gradient(g)
+    for x in (np.nan, np.inf, -1e200):
+        for axis in range(3):
+            p = inputs.small_problem(56, n_atoms=n_atoms, shape=(16, 18, 20), radius=5.0)
+            p.solute.xyz[2, axis] = x
+            got = _solver(R, p)[0].sfe_gradient(g)
+            others = [a for a in range(n_atoms) if a != 2]
+            assert torch.equal(got[others], ref[others])
+            for c in range(3):
+                if np.isnan(x) or (np.isinf(x) and c == axis):
+                    assert torch.isnan(got[2, c])
+                else:
+                    assert got[2, c] == 0.0
+
+
 def test_no_atoms_and_bad_arguments(R):
     prob = inputs.small_problem(4, n_atoms=3, shape=(16, 16, 16), radius=1.5)
     chi, dk = inputs.solvent_table_for(prob.solvent)

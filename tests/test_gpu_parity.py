@@ -153,6 +153,31 @@ def test_potential_points_per_thread(R, O, shape):
     assert (np.abs(phi - phi_ref) / np.maximum(1.0, np.abs(phi_ref))).max() < 1.5e-7
 
 
+@pytest.mark.parametrize("shape", [(64, 128, 128), (30, 20, 18)])
+def test_potential_of_an_atom_out_of_range(R, shape):
+    """A NaN coordinate makes every value NaN, with or without a charge.  An atom
+    at an infinite coordinate, or one whose squared distance overflows, adds
+    exactly nothing."""
+    prob = inputs.small_problem(4, n_atoms=4, shape=shape, radius=2.0)
+    fields = {}
+    for x in (np.nan, np.inf, -1e200, None):
+        for axis in range(3):
+            sol = prob.solute
+            p = inputs.small_problem(4, n_atoms=4, shape=shape, radius=2.0)
+            if x is None:
+                p.solute = inputs.Solute(sol.xyz[1:], sol.q[1:], sol.sigma[1:], sol.eps[1:])
+            else:
+                p.solute.xyz[0, axis] = x
+                p.solute.q[0] *= axis > 0
+            print(f"potential {shape} coordinate {axis} = {x}", flush=True)
+            fields[x, axis] = [t.clone() for t in _run(R, p)[0].fields()]
+    for axis in range(3):
+        for i, alone in enumerate(fields[None, 0]):
+            assert torch.isnan(fields[np.nan, axis][i]).all()
+            assert torch.equal(fields[np.inf, axis][i], alone)
+            assert torch.equal(fields[-1e200, axis][i], alone)
+
+
 # (saline, (nz, ny, nx)): the generic path, the fused x kernels with the fused
 # z transform + contraction, and every fused instantiation the workloads reach
 # at full size: x and z lengths 96 (96^3 batch members), x 256 and z 256 (the
