@@ -496,11 +496,11 @@ SiteConsts site_consts(const rism3d_problem* pr, double beta) {
 
 unsigned blocks_for(size_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
 
-template <int NV, int K>
+template <int NV, int K, bool STAGE>
 void launch_potential_k(const Layout& L, void* ws, double dr, const SiteConsts& sc,
                         hipStream_t s) {
   TIMED(F_POTENTIAL, s);
-  hipLaunchKernelGGL((k_potential<NV, K>), dim3(blocks_for(L.N / K, kPotThreads)),
+  hipLaunchKernelGGL((k_potential<NV, K, STAGE>), dim3(blocks_for(L.N / K, kPotThreads)),
                      dim3(kPotThreads), 0, s, at<double4>(ws, L.off_atoms),
                      at<double2>(ws, L.off_lj), L.n_atoms, L.nx, L.ny, L.nz, dr, sc,
                      at<float>(ws, L.off_w), at<float>(ws, L.off_phi));
@@ -508,12 +508,14 @@ void launch_potential_k(const Layout& L, void* ws, double dr, const SiteConsts& 
 
 // Four points a thread from 2^20 points on (rows of a multiple of four): 5
 // sites, 200 atoms at 128^3 642 us against 689 with two.  Smaller grids need the
-// threads: 96^3 364 with four, 347 with two; 64^3 157 and 123.
+// threads: 96^3 364 with four, 347 with two; 64^3 157 and 123; and below 2^18
+// points one a thread with the atoms in LDS (figures at k_potential).
 template <int NV>
 void launch_potential_nv(const Layout& L, void* ws, double dr, const SiteConsts& sc,
                          hipStream_t s) {
-  if (L.nx % 4 == 0 && L.N >= ((size_t)1 << 20)) launch_potential_k<NV, 4>(L, ws, dr, sc, s);
-  else launch_potential_k<NV, 2>(L, ws, dr, sc, s);
+  if (L.N < ((size_t)1 << 18)) launch_potential_k<NV, 1, true>(L, ws, dr, sc, s);
+  else if (L.nx % 4 == 0 && L.N >= ((size_t)1 << 20)) launch_potential_k<NV, 4, false>(L, ws, dr, sc, s);
+  else launch_potential_k<NV, 2, false>(L, ws, dr, sc, s);
 }
 
 void launch_potential(const Layout& L, void* ws, double dr, const SiteConsts& sc, hipStream_t s) {

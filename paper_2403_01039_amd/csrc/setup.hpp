@@ -8,12 +8,14 @@
 namespace rism {
 
 constexpr int kPotThreads = 256;
+constexpr int kPotChunk = 256;   // atoms staged in LDS at a time
 
-// K consecutive floats in one store (K = 2 or 4, p aligned to it).
+// K consecutive floats in one store (K = 1, 2 or 4, p aligned to it).
 template <int K>
 __device__ __forceinline__ void store_k(float* __restrict__ p, const float* v) {
   if constexpr (K == 4) *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-  else *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
+  else if constexpr (K == 2) *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
+  else p[0] = v[0];
 }
 
 // A coordinate within 2^510, so that squared distances stay finite and 1/d^3 is 0
@@ -101,13 +103,22 @@ struct ExpNeg {
 // evaluated where no point of the wave is nearer).  128^3, 200 atoms, 5 sites: 1439 us with a square root,
 // two divisions and the library's exp at one point a thread, 642 us now (45 FP64
 // operations a pair, 0.75 of the FP64 issue rate).
-template <int NV, int K>
+//
+// A small grid has too few waves to hide the scalar loads, whose data, just
+// written, is in no nearby cache: it waits for memory atom after atom.  STAGE
+// copies the atoms to LDS, a workgroup's loads at once, and one point a thread
+// keeps the most waves.  200 atoms, 3 sites: 32^3 59 us staged, 120 with scalar
+// loads and two points a thread; 48^3 69 and 121; 64^3 106 and 113, and beyond it
+// the LDS reads beside the FP64 operations lose.
+template <int NV, int K, bool STAGE>
 __global__ __launch_bounds__(kPotThreads) void k_potential(
     const double4* __restrict__ atoms, const double2* __restrict__ lj, int n_atoms, int nx, int ny,
     int nz, double dr, SiteConsts sc, float* __restrict__ w, float* __restrict__ phi_out) {
   const size_t N = (size_t)nx * ny * nz;   // a multiple of K, as nx is
   const unsigned idx = (blockIdx.x * kPotThreads + threadIdx.x) * K;   // N <= 512^3
-  if (idx >= N) return;
+  if (!STAGE && idx >= N) return;   // (staged: every thread copies)
+  __shared__ double4 s_at[STAGE ? kPotChunk : 1];
+  __shared__ double2 s_lj[STAGE ? kPotChunk * NV : 1];
   const unsigned row = idx / (unsigned)nx;
   const int ix = (int)(idx - row * nx), iz = (int)(row / (unsigned)ny), iy = (int)(row - iz * ny);
   const double py = iy * dr, pz = iz * dr;
@@ -121,8 +132,17 @@ __global__ __launch_bounds__(kPotThreads) void k_potential(
   }
   const ExpNeg ex;
   for (int a = 0; a < n_atoms; ++a) {
-    const double4 at = atoms[a];
-    const double2* la = lj + (size_t)a * NV;
+    if constexpr (STAGE) {
+      if (a % kPotChunk == 0) {
+        const int cnt = n_atoms - a < kPotChunk ? n_atoms - a : kPotChunk;
+        __syncthreads();   // the previous atoms are read
+        for (int t = threadIdx.x; t < cnt; t += kPotThreads) s_at[t] = atoms[a + t];
+        for (int t = threadIdx.x; t < cnt * NV; t += kPotThreads) s_lj[t] = lj[(size_t)a * NV + t];
+        __syncthreads();
+      }
+    }
+    const double4 at = STAGE ? s_at[a % kPotChunk] : atoms[a];
+    const double2* la = STAGE ? s_lj + a % kPotChunk * NV : lj + (size_t)a * NV;
     const double dy = py - at.y, dz = pz - at.z;
     const double dyz = dy * dy + dz * dz;
     double d2[K], inv[K], q[K];
@@ -166,6 +186,7 @@ __global__ __launch_bounds__(kPotThreads) void k_potential(
       }
     }
   }
+  if (STAGE && idx >= N) return;
 #pragma unroll
   for (int k = 0; k < K; ++k) phi[k] -= phi_sr[k];   // phi_lr
 #pragma unroll

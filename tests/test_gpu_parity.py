@@ -153,6 +153,25 @@ def test_potential_points_per_thread(R, O, shape):
     assert (np.abs(phi - phi_ref) / np.maximum(1.0, np.abs(phi_ref))).max() < 1.5e-7
 
 
+@pytest.mark.parametrize("n_atoms,shape", [(1, (4, 6, 2)), (256, (18, 10, 12)),
+                                           (257, (16, 16, 16)), (600, (18, 10, 12))])
+def test_potential_of_small_grids(R, O, n_atoms, shape):
+    """Grids below 2^18 points, whose atoms are staged in chunks of 256: one atom, a
+    whole chunk, remainders of 1 and 88, and grids that fill no whole workgroup.
+    Bar as for the points a thread."""
+    prob = inputs.small_problem(4, n_atoms=4, shape=shape, radius=2.0)
+    prob.solute = inputs.random_solute(4, n_atoms, (21.0, 21.0, 21.0))
+    print(f"potential {shape} {n_atoms} atoms", flush=True)
+    s, chi, dk = _run(R, prob)
+    w, phi = (t.cpu().numpy() for t in s.fields())
+    sys_ = O.build_system(prob, chi, dk)
+    w_ref = sys_.beta_u - sys_.f
+    q_v = prob.solvent.site_arrays()[0]
+    phi_ref = sys_.f[0] / (sys_.beta * O.COULOMB * q_v[0])
+    assert (np.abs(w - w_ref) / np.maximum(1.0, np.abs(w_ref))).max() < 1.5e-7
+    assert (np.abs(phi - phi_ref) / np.maximum(1.0, np.abs(phi_ref))).max() < 1.5e-7
+
+
 @pytest.mark.parametrize("shape", [(64, 128, 128), (30, 20, 18)])
 def test_potential_of_an_atom_out_of_range(R, shape):
     """A NaN coordinate makes every value NaN, with or without a charge.  An atom
