@@ -240,6 +240,10 @@ bool plan_axis(int n, FlexPlan* p) {
 // a tile that the plan's registers transform in one go, in at most 32 KB of LDS.
 constexpr size_t kFlexTileBytes = 32768;
 
+size_t flex_lds(const FlexPlan& P, int lines, size_t elem) {
+  return ((size_t)lines * P.pitch + 2 * P.n) * elem;
+}
+
 // Rows per workgroup: about 1024 workgroups, but at least 8 rows each (2880
 // workgroups of 4 rows take 17.1 us on 120-point rows, 17 rows 11.1).
 int flex_rows(const FlexPlan& P, size_t elem, size_t rows) {
@@ -257,17 +261,16 @@ int flex_update_rows(const FlexPlan& P, size_t elem, size_t rows) {
 
 // Columns per workgroup: whole 128-byte segments of FP32 pairs, 16, 24 or 32,
 // whichever pads nx least (120: 24 columns 11.9 us, 30 columns 14.9, 16 13.6;
-// 160: 16 columns 20.1, 32 26.2).
+// 160: 16 columns 20.1, 32 26.2).  Long FP64 lines, of which 32 KB hold three, take
+// four all the same, 64 bytes of a row (two pairs of 64 x 500 x 64, FP64 y pass: 51 us,
+// two columns 82).
 int flex_cols(const FlexPlan& P, size_t elem, int nx) {
-  const int most = (int)std::min<size_t>(P.cap / P.n, kFlexTileBytes / (P.pitch * elem));
+  int most = (int)std::min<size_t>(P.cap / P.n, kFlexTileBytes / (P.pitch * elem));
+  if (most < 4 && flex_lds(P, 4, elem) <= (size_t)kFlexMaxLds) most = std::min(P.cap / P.n, 4);
   int best = std::max(1, std::min(most, 16) & ~1);
   for (int l : {24, 32})
     if (l <= most && (nx + l - 1) / l * l < (nx + best - 1) / best * best) best = l;
   return best;
-}
-
-size_t flex_lds(const FlexPlan& P, int lines, size_t elem) {
-  return ((size_t)lines * P.pitch + 2 * P.n) * elem;
 }
 
 // Columns per side and workgroup of the flexible z kernel (even, at most 8): what

@@ -259,6 +259,14 @@ def test_maps_at_flexible_lengths(R, O, saline, shape, closure):
     assert np.abs(res - ref).max() < 2e-6 * max(1.0, np.abs(ref).max())
 
 
+# FP64 lines of more than 455 points, four columns a tile, with a remainder of two.
+@pytest.mark.parametrize("saline,shape", [(False, (6, 480, 18)), (True, (486, 4, 10)),
+                                          (False, (2, 500, 4))])
+def test_maps_at_long_lines(R, O, saline, shape):
+    """Bars of the two map tests."""
+    test_maps_at_flexible_lengths(R, O, saline, shape, "kh")
+
+
 def test_map_of_unaligned_tau(R, O):
     """A tau at 4 bytes past a 16-byte boundary takes the start's one-float copies:
     the same values reach the same kernels, so the residual has the same bits."""
