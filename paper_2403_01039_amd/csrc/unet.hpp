@@ -156,8 +156,8 @@ __device__ __forceinline__ void conv_store(const ConvArgs& p, int N, size_t v, i
 // Bound by the LDS reads: an operand of 1 KB feeds MT instructions of 16 cycles
 // on each of four SIMDs, so one output tile can reach half of the matrix rate and
 // two all of it; below that by staging, whose index arithmetic and latency are
-// kept small (one row of the halo per thread group, loads in batches, three waves
-// a SIMD).  Before and after, at 128^3: 16 -> 16 channels 78 -> 52 us, 48 -> 16 215
+// kept small (one row of the halo per thread group, loads in batches, two or three
+// waves a SIMD).  Before and after, at 128^3: 16 -> 16 channels 78 -> 52 us, 48 -> 16 215
 // -> 121 us (0.29 of the BF16 peak), and at 64^3 96 -> 32 136 -> 45 us (0.39).
 constexpr int kTileX = 16, kTileZ = 4;
 constexpr int kHaloX = kTileX + 2, kHaloZ = kTileZ + 2;
@@ -176,11 +176,23 @@ __host__ __device__ constexpr size_t conv_packed(int cout, int cin) {
 // staging loads a thread has in flight, out of n: in as few batches of at most 9
 __host__ __device__ constexpr int conv_batch(int n) { return (n + (n + 8) / 9 - 1) / ((n + 8) / 9); }
 
+// staged units of a chunk
+__host__ __device__ constexpr int conv_halo(int cgc, int ty) {
+  return kHaloZ * (ty + 2) * cgc * kHaloX;
+}
+// waves a SIMD that the kernel asks for: three, but two where the LDS holds no third
+// workgroup, and for three groups and two output tiles, whose 21 offsets and 16
+// accumulator tiles spill in the registers of three (24 -> 32 channels, 128^3:
+// forward of the network 668 us with three, 630 with two)
+__host__ __device__ constexpr int conv_waves(int cgc, int ty, int mt) {
+  return 3 * conv_halo(cgc, ty) * 16 > 160 * 1024 || (ty == 8 && cgc == 3 && mt == 2) ? 2 : 3;
+}
+
 template <int EPI, int CGC, int TY, int MT>
-__global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(conv_waves(CGC, TY, MT))))
 void k_conv3(ConvArgs p) {
   constexpr int kTileY = TY, kHaloY = TY + 2, NQ = 27 * CGC, NS = conv_steps(CGC);
-  __shared__ __align__(16) u32x4 halo[kHaloZ * kHaloY * CGC * kHaloX];
+  __shared__ __align__(16) u32x4 halo[conv_halo(CGC, TY)];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = lane & 15, g = lane >> 4;
   const int N = p.nz * p.ny * p.nx;

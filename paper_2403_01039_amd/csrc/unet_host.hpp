@@ -184,7 +184,7 @@ void net_pack(const NetPlan& P, const float* params, void* ws, bool flipped, hip
 }
 
 // One convolution (channel counts are multiples of 8): the halo-tiled
-// kernel, staging conv_chunk() channel groups (at most 64 KB of LDS) at a time.
+// kernel, staging conv_chunk() channel groups (at most 67.5 KB of LDS) at a time.
 // Tiles of 16 x 8 x 4 voxels, or 16 x 2 x 4 where those would give fewer than 512
 // workgroups (the coarse levels); two output tiles a workgroup where that leaves
 // 512 workgroups (64^3, 96 -> 32 channels: 85 us with one, 45 with two; three, for

@@ -218,6 +218,49 @@ def test_gradient_on_ragged_tiles(R, monkeypatch, levels, base, shape):
             off += n
 
 
+# Two output tiles a workgroup on the large tiling with two and with three channel
+# groups (16 and 24 input channels) and, in the data gradient, three (40 outputs).
+@pytest.mark.parametrize("cin,cout", [(16, 3), (24, 40)])
+def test_two_output_tiles(R, monkeypatch, cin, cout):
+    """The network of test_gradient_on_ragged_tiles: its output is exact, every sum
+    being one of few small multiples of 1/16, and the gradients' bar is the same."""
+    from oracle import unet as U
+    shape = (61, 57, 49)
+    print(f"unet output and gradient {cin} -> 32 -> 32 -> {cout}, {shape}", flush=True)
+    cfg = R.unet_config(cin, cout, levels=1, base=32, slope=0.25)
+    ocfg = U.Config(levels=1, base=32, in_channels=cin, out_channels=cout, slope=0.25)
+    rng = np.random.default_rng(62)
+    parts = []
+    for _, ci, co in ocfg.layers():
+        w = np.zeros((co, 27 * ci))
+        for o in range(co):
+            w[o, rng.choice(27 * ci, 3, replace=False)] = rng.choice([-1.0, 1.0], 3)
+        parts += [w.ravel(), rng.integers(-1, 2, co)]
+    theta = np.concatenate(parts).astype(np.float32)
+    x = rng.integers(-2, 3, shape + (cin,)).astype(np.float32)
+    target = rng.integers(-3, 4, shape + (cout,)).astype(np.float64)
+    params = torch.tensor(theta, device="cuda")
+    out = torch.empty((cout,) + shape, dtype=torch.float32, device="cuda")
+    grad = torch.empty_like(params)
+    ws = R.alloc_workspace(R.unet_workspace_bytes(cfg, shape, True))
+    R.unet_forward(cfg, params, _site_major(x), out, ws)
+    R.unet_gradient(cfg, params, _site_major(x), _site_major(target), grad, ws)
+    leaky, mse, leaky_bwd = U.leaky, U.mse, U.leaky_backward
+    r = lambda a: bf16_round(a).astype(np.float64)
+    monkeypatch.setattr(U, "leaky", lambda v, sl: r(leaky(v, sl)))
+    monkeypatch.setattr(U, "mse", lambda o, t: (mse(o, t)[0], r(mse(o, t)[1])))
+    monkeypatch.setattr(U, "leaky_backward", lambda y, d, sl: r(leaky_bwd(y, d, sl)))
+    ref_out, _ = U.forward(ocfg, theta.astype(np.float64), x.astype(np.float64))
+    assert np.array_equal(out.cpu().numpy(), np.moveaxis(ref_out, -1, 0))
+    _, ref = U.loss_and_grad(ocfg, theta.astype(np.float64), x.astype(np.float64), target)
+    g, off = grad.cpu().numpy(), 0
+    for name, ci, co in ocfg.layers():
+        for part, n in (("W", co * 27 * ci), ("b", co)):
+            got, want = g[off:off + n], ref[off:off + n]
+            assert np.abs(got - want).max() <= 1e-4 * np.abs(want).max(), (name, part)
+            off += n
+
+
 def test_gradient_is_bitwise_reproducible(R):
     """The weight and bias gradients are summed over workgroups in a fixed
     order (per-workgroup slabs, then a slab sum), so two evaluations agree
