@@ -280,6 +280,26 @@ def test_map_of_unaligned_tau(R, O):
     assert torch.equal(s.map(shifted)[0], s.map(tau)[0])
 
 
+@pytest.mark.parametrize("offset", [1, 2, 3])
+def test_residual_to_unaligned_output(R, O, offset):
+    """A residual output off the 16-byte boundary takes the one-float copy, with the
+    same bits; what lies around it is not written."""
+    prob, s, sys_ = _map_case(R, O, True, (18, 20, 24), "kh")
+    rng = np.random.default_rng(29)
+    tau = torch.tensor(0.05 * rng.standard_normal(sys_.f.shape), dtype=torch.float32, device="cuda")
+    flat = torch.full((tau.numel() + 8,), -7.0, device="cuda")
+    out = flat[offset:offset + tau.numel()].view(tau.shape)
+    assert out.data_ptr() % 16 == 4 * offset
+    rms = R.rism3d_map(s.dp, s.opts, s.ws, tau, out)
+    ref, ref_rms = s.map(tau)
+    assert torch.equal(out, ref) and rms == ref_rms
+    assert (flat[:offset] == -7.0).all() and (flat[offset + tau.numel():] == -7.0).all()
+    out.fill_(-7.0)
+    R.rism3d_map_increment(s.dp, s.opts, s.ws, tau, 0.5 * tau, out)
+    assert torch.equal(out, s.map_increment(tau, 0.5 * tau)[0])
+    assert (flat[:offset] == -7.0).all() and (flat[offset + tau.numel():] == -7.0).all()
+
+
 # Remainders of the default tiles on fixed lengths: 180 x rows against 8, y lines
 # against 16, z columns against 8 (3 sites) and 4 (5 sites).
 @pytest.mark.parametrize("saline,shape", [(True, (10, 6, 64)), (True, (6, 10, 32)),
