@@ -38,19 +38,15 @@ def kernel_bytes(nv: int, N: int, M: int, m_avg: float, fam: str) -> float:
     the packed spectra.  The FP32 increment scheme moves more than that (see
     increment_overhead_bytes)."""
     P = (nv + 1) // 2
-    if fam == "update_closure_f32":   # read m tau_i, m R_i, w; write tau; write spectra
-        return nv * N * 4 * (2 * m_avg + 2) + 8 * P * N
-    if fam == "update_closure_f64":   # read m tau_i, m R_i, w, tau_ref; write tau; FP64 spectra
-        return nv * N * 4 * (2 * m_avg + 3) + 16 * P * N
     if fam.startswith("fft_") and fam.endswith("_f32") or fam in ("contract_f32",
                                                                    "zfft_contract_f32"):
         return 16 * P * N
     if fam.startswith("fft_") and fam.endswith("_f64") or fam in ("contract_f64",
                                                                    "zfft_contract_f64"):
         return 32 * P * N
-    if fam == "update_fftx_f32":      # update + closure, spectra written once after the x pass
+    if fam == "update_fftx_f32":      # read m tau_i, m R_i, w; write tau; write spectra
         return nv * N * 4 * (2 * m_avg + 2) + 8 * P * N
-    if fam == "update_fftx_f64":
+    if fam == "update_fftx_f64":      # read m tau_i, m R_i, w, tau_ref; write tau; FP64 spectra
         return nv * N * 4 * (2 * m_avg + 3) + 16 * P * N
     if fam == "fftx_residual_f32":    # spectra read once, then the residual + Gram row
         return 8 * P * N + nv * N * 4 * (2 + max(m_avg - 1, 0) + 1)
@@ -70,14 +66,13 @@ def increment_overhead_bytes(nv: int, N: int, fam: str) -> float:
     increment dg (read back by the residual in place of tau and w, so the
     residual's count is unchanged; the update reads the anchor's closure
     argument d_ref in place of w)."""
-    if fam in ("update_fftx_f32", "update_closure_f32"):
+    if fam == "update_fftx_f32":
         return 4.0 * nv * N
     return 0.0
 
 
 ITERATION_FAMILIES = ("update_fftx_f32", "fft_y_f32", "zfft_contract_f32", "fftx_residual_f32",
-                      "update_closure_f32", "fft_x_f32", "fft_z_f32", "contract_f32",
-                      "residual_gram_f32")
+                      "fft_x_f32", "fft_z_f32", "contract_f32", "residual_gram_f32")
 
 
 def host_cpu():

@@ -151,6 +151,32 @@ __device__ inline float closure_dg(float dref, float delta, int kind, int order)
   return closure_g(dnew, kind, order) - closure_g(dref, kind, order);
 }
 
+// V consecutive floats (V = 4: one 16-byte access, V = 2: one of 8 bytes).
+template <int V>
+__device__ inline void ldv(const float* __restrict__ p, float* o) {
+  if constexpr (V == 4) {
+    const float4 t = *reinterpret_cast<const float4*>(p);
+    o[0] = t.x; o[1] = t.y; o[2] = t.z; o[3] = t.w;
+  } else if constexpr (V == 2) {
+    const float2 t = *reinterpret_cast<const float2*>(p);
+    o[0] = t.x; o[1] = t.y;
+  } else {
+#pragma unroll
+    for (int i = 0; i < V; ++i) o[i] = p[i];
+  }
+}
+template <int V>
+__device__ inline void stv(float* __restrict__ p, const float* v) {
+  if constexpr (V == 4) {
+    *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+  } else if constexpr (V == 2) {
+    *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < V; ++i) p[i] = v[i];
+  }
+}
+
 // 1 / sqrt(a) in FP64 (a normal, positive): the hardware estimate (relative error
 // e0 ~ 2^-24) and one step of third order, y (1 + e/2 + 3 e^2 / 8) with
 // e = 1 - a y^2, whose own error is of order e0^3, below FP64 round-off.

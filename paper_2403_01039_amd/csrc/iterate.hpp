@@ -70,32 +70,6 @@ __global__ void k_init_state(IterState* st, float eta, int warm) {
   st->hold = 0;
 }
 
-// V consecutive floats (V = 4: one 16-byte access, V = 2: one of 8 bytes).
-template <int V>
-__device__ inline void ldv(const float* __restrict__ p, float* o) {
-  if constexpr (V == 4) {
-    const float4 t = *reinterpret_cast<const float4*>(p);
-    o[0] = t.x; o[1] = t.y; o[2] = t.z; o[3] = t.w;
-  } else if constexpr (V == 2) {
-    const float2 t = *reinterpret_cast<const float2*>(p);
-    o[0] = t.x; o[1] = t.y;
-  } else {
-#pragma unroll
-    for (int i = 0; i < V; ++i) o[i] = p[i];
-  }
-}
-template <int V>
-__device__ inline void stv(float* __restrict__ p, const float* v) {
-  if constexpr (V == 4) {
-    *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-  } else if constexpr (V == 2) {
-    *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < V; ++i) p[i] = v[i];
-  }
-}
-
 // Place the starting tau (the caller's, or zero) in history slot 0, where the
 // first update reads it; keeps the iteration kernels independent of the call.
 // The start: tau_ref = tau0 (or 0) and delta = 0 in the first slot.
@@ -610,7 +584,7 @@ __device__ inline void write_partials(const double* acc, int M, double* __restri
   }
 }
 
-template <bool ANCHOR, int V, int MM = kMaxDepth>
+template <bool ANCHOR, int MM = kMaxDepth>
 __global__ __launch_bounds__(kRedThreads) void k_residual(
     const IterState* __restrict__ st, const void* __restrict__ spec, const float* __restrict__ w,
     float* __restrict__ tau_hist, float* __restrict__ res_hist, float* __restrict__ tau_ref,
@@ -624,6 +598,7 @@ __global__ __launch_bounds__(kRedThreads) void k_residual(
   double acc[MM + 1];
 #pragma unroll
   for (int i = 0; i <= MM; ++i) acc[i] = 0.0;
+  constexpr int V = 4;   // points a thread and step (N is a multiple of 8)
   const size_t NQ = N / V;
   const size_t total = (size_t)npair * NQ;
   for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < total;
@@ -644,12 +619,8 @@ __global__ __launch_bounds__(kRedThreads) void k_residual(
     } else {
       const float* sp = reinterpret_cast<const float*>(static_cast<const float2*>(spec) + o);
       float pk[2 * V];
-      if constexpr (V == 4) {
-        ldv<4>(sp, pk);
-        ldv<4>(sp + 4, pk + 4);
-      } else {
-        ldv<2 * V>(sp, pk);
-      }
+      ldv<4>(sp, pk);
+      ldv<4>(sp + 4, pk + 4);
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         hre[v] = pk[2 * v];
@@ -1163,12 +1134,6 @@ __global__ __launch_bounds__(kSfeReduceThreads) void k_sfe_reduce(
     for (int g = 0; g < nv; ++g) total += site[g];
     out[kMaxSites] = total;
   }
-}
-
-// Copy of one history slot (the residual of a single map evaluation).
-__global__ void k_copy_floats(const float* __restrict__ src, float* __restrict__ dst, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = src[i];
 }
 
 // The history slot of the accepted iterate (final_slot) of n = nv N floats; V as in

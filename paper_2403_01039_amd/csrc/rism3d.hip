@@ -69,14 +69,13 @@ rism3d_status fail(rism3d_status s, const char* fmt, ...) {
 // Optional per-family kernel timing with HIP events (thread-local).
 // ---------------------------------------------------------------------------
 enum Family {
-  F_UPDATE32, F_UPDATE64, F_FFTX32, F_FFTY32, F_FFTZ32, F_FFTX64, F_FFTY64, F_FFTZ64,
+  F_FFTX32, F_FFTY32, F_FFTZ32, F_FFTX64, F_FFTY64, F_FFTZ64,
   F_CONTRACT32, F_CONTRACT64, F_RESIDUAL32, F_RESIDUAL64, F_CONTROL, F_UPDFFT32, F_UPDFFT64,
   F_FFTRES32, F_FFTRES64, F_ZCZ32, F_ZCZ64, F_POTENTIAL, F_FTILDE, F_SETUP, F_OUTPUT, F_SFE,
   F_NET_FWD, F_NET_GRAD, F_HALFSTEP, F_SFEGRAD, F_COUNT
 };
 const char* const kFamilyNames[F_COUNT] = {
-    "update_closure_f32", "update_closure_f64", "fft_x_f32", "fft_y_f32", "fft_z_f32",
-    "fft_x_f64", "fft_y_f64", "fft_z_f64", "contract_f32", "contract_f64", "residual_gram_f32",
+    "fft_x_f32", "fft_y_f32", "fft_z_f32", "fft_x_f64", "fft_y_f64", "fft_z_f64", "contract_f32", "contract_f64", "residual_gram_f32",
     "residual_gram_f64", "mdiis_control", "update_fftx_f32", "update_fftx_f64",
     "fftx_residual_f32", "fftx_residual_f64", "zfft_contract_f32", "zfft_contract_f64",
     "potential", "long_range_spectrum",
@@ -724,7 +723,7 @@ void launch_axis(const Layout& L, C* spec, const C* const tw[3], int axis, int f
 
 // Forward (forward != 0) or inverse 3D transform of all packed pairs, one
 // kernel per axis; C = float2 (bulk) or double2 (anchor).  Common lengths use
-// the fixed-size kernels, others the generic runtime-plan kernel.
+// the fixed-size kernels, others those of flex.hpp.
 template <typename C>
 void launch_fft3_on(const Layout& L, C* spec, const C* const tw[3], int forward, const int* done,
                     hipStream_t s, bool skip_x = false) {
@@ -959,15 +958,15 @@ void launch_flex_update(const Layout& L, void* ws, const rism3d_opts* op, hipStr
                      lines, at<C>(ws, ANCHOR ? L.off_tw64[0] : L.off_tw32[0]));
 }
 
-template <bool ANCHOR, int V>
+template <bool ANCHOR>
 void launch_residual(const Layout& L, void* ws, const rism3d_opts* op, unsigned nblk,
                      hipStream_t s) {
   TIMED(ANCHOR ? F_RESIDUAL64 : F_RESIDUAL32, s);
   // as in the fused residual, the tightest bound of the depth: fewer sums a thread
-  auto k = &k_residual<ANCHOR, V, kMaxDepth>;
+  auto k = &k_residual<ANCHOR, kMaxDepth>;
   if constexpr (!ANCHOR) {
-    if (L.M <= 3) k = &k_residual<false, V, 3>;
-    else if (L.M <= 5) k = &k_residual<false, V, 5>;
+    if (L.M <= 3) k = &k_residual<false, 3>;
+    else if (L.M <= 5) k = &k_residual<false, 5>;
   }
   hipLaunchKernelGGL(k, dim3(nblk), dim3(kRedThreads), 0, s,
                      at<IterState>(ws, L.off_state), at<void>(ws, L.off_spec),
@@ -995,13 +994,10 @@ void launch_flex(const Layout& L, void* ws, const rism3d_opts* op, bool anchor, 
   const double2* tw64[3] = {at<double2>(ws, L.off_tw64[0]), nullptr, nullptr};
   if (anchor) launch_axis(L, at<double2>(ws, L.off_spec), tw64, 0, 0, done, s);
   else launch_axis(L, at<float2>(ws, L.off_spec), tw32, 0, 0, done, s);
-  const bool v4 = L.N % 4 == 0;
-  const unsigned nblk = std::min<unsigned>(
-      blocks_for((size_t)L.npair * (v4 ? L.N / 4 : L.N), kRedThreads), kRedBlocks);
-  if (anchor && v4) launch_residual<true, 4>(L, ws, op, nblk, s);
-  else if (anchor) launch_residual<true, 1>(L, ws, op, nblk, s);
-  else if (v4) launch_residual<false, 4>(L, ws, op, nblk, s);
-  else launch_residual<false, 1>(L, ws, op, nblk, s);
+  const unsigned nblk =
+      std::min<unsigned>(blocks_for((size_t)L.npair * (L.N / 4), kRedThreads), kRedBlocks);
+  if (anchor) launch_residual<true>(L, ws, op, nblk, s);
+  else launch_residual<false>(L, ws, op, nblk, s);
   launch_control(L, ws, op, anchor, nblk, s, Batch{});
 }
 
@@ -2040,7 +2036,6 @@ rism3d_status rism3d_map(const rism3d_problem* pr, const rism3d_opts* op, const 
     hipLaunchKernelGGL(k_hold_final, dim3(1), dim3(1), 0, s, dst);
   }
   launch_iteration(L, ws, &one, (1.0 / pr->dk), true, s);
-  const size_t n = (size_t)L.nv * L.N;
   launch_copy_residual(L, ws, d_res, s);
   LAUNCH_CHECK();
   HIP_TRY(hipMemcpyAsync(&host, dst, sizeof(IterState), hipMemcpyDeviceToHost, s));

@@ -10,14 +10,6 @@ namespace rism {
 constexpr int kPotThreads = 256;
 constexpr int kPotChunk = 256;   // atoms staged in LDS at a time
 
-// K consecutive floats in one store (K = 1, 2 or 4, p aligned to it).
-template <int K>
-__device__ __forceinline__ void store_k(float* __restrict__ p, const float* v) {
-  if constexpr (K == 4) *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-  else if constexpr (K == 2) *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
-  else p[0] = v[0];
-}
-
 // A coordinate within 2^510, so that squared distances stay finite and 1/d^3 is 0
 // (kFarAway: an infinite one); NaN stays NaN.
 __device__ __forceinline__ double in_range(double x) {
@@ -198,12 +190,12 @@ __global__ __launch_bounds__(kPotThreads) void k_potential(
       const double u = acc[k][g] + coul * phi_sr[k];
       o[k] = (float)((u + coul * phi[k] > kBetaUCap) ? kBetaUCap - coul * phi[k] : u);
     }
-    store_k<K>(w + (size_t)g * N + idx, o);
+    stv<K>(w + (size_t)g * N + idx, o);
   }
   float o[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) o[k] = (float)phi[k];
-  store_k<K>(phi_out + idx, o);
+  stv<K>(phi_out + idx, o);
 }
 
 __device__ inline double kappa_of(int j, int n, double dk) {
