@@ -25,9 +25,9 @@
 //
 // With one atom a lane the n_v + 5 LDS reads of a point cost the compute unit
 // more cycles than the pair's FP64 arithmetic; with two the arithmetic bounds
-// (200 atoms, 128^3, 5 sites: 765 us at A = 1, 690 at 2, 675 at 4, which wastes
-// more lanes at other atom counts; 1230 us before, with a square root and a
-// division for 1/d and one atom a lane).  At most 32 atoms leave lanes over: the
+// (200 atoms, 128^3, 5 sites, repeated back to back: 765 us at A = 1, 690 at 2, 675
+// at 4, which wastes more lanes at other atom counts; 1230 us before, with a square
+// root and a division for 1/d and one atom a lane).  At most 32 atoms leave lanes over: the
 // wave then takes 2 or 4 points at a time, each for `lanes` = 32 or 16 lanes.
 #pragma once
 

@@ -780,10 +780,11 @@ void launch_zcz_b(const Layout& L, void* ws, double inv_dkt, const int* done, hi
 // Default columns a side of the FP32 z kernel.  Tiles of 24 to 32 columns in all
 // leave several workgroups a CU to overlap the phases of (3 sites: at 64^3 6.8 us,
 // 16 columns a side 9.7; at 96^3 19.3, 20.4; 5 sites at 128^3: 4 columns a side 35.9,
-// 8 columns 40.2).  Elsewhere a narrower tile fills no whole round of a workgroup's
-// butterflies, whose guarded code rounds differently in the last bit, which a solve
-// carries to its tolerance; the widest tile in 64 KB stays (5 sites at 64^3: 15.2,
-// 4 columns 8.3).
+// 8 columns 40.2).  They are the default where they give the bits of the widest tile
+// in 64 KB, which stays elsewhere: every width is compiled apart, the compiler chooses
+// the products of the butterflies that it fuses, and a solve carries the last bit to
+// its tolerance.  The lengths chosen are thus those of this compiler, and one that
+// would gain most is left (5 sites at 64^3: 15.2 us, 4 columns a side 8.3).
 template <int NZ, int NV>
 constexpr int zcz32_cols() {
   constexpr int P = (NV + 1) / 2;

@@ -92,9 +92,11 @@ struct ExpNeg {
 // loads), and dy^2 + dz^2; and their K independent chains hide the FP64
 // latency.  1/dc and dc come from one reciprocal square root, e^{-d} from
 // ExpNeg; beyond 38 A it adds below FP64 resolution and is taken as 0 (and not
-// evaluated where no point of the wave is nearer).  128^3, 200 atoms, 5 sites: 1439 us with a square root,
-// two divisions and the library's exp at one point a thread, 642 us now (45 FP64
-// operations a pair, 0.75 of the FP64 issue rate).
+// evaluated where no point of the wave is nearer).  128^3, 200 atoms, 5 sites: 1439 us
+// with a square root, two divisions and the library's exp at one point a thread, 642
+// us now (45 FP64 operations a pair, 0.75 of the FP64 issue rate), both repeated back
+// to back.  Behind the kernels that write the atoms a trace has 1446 and 760 us: the
+// scalar loads then wait for memory (0.63 of the issue rate).
 //
 // A small grid has too few waves to hide the scalar loads, whose data, just
 // written, is in no nearby cache: it waits for memory atom after atom.  STAGE

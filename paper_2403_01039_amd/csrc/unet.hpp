@@ -157,8 +157,9 @@ __device__ __forceinline__ void conv_store(const ConvArgs& p, int N, size_t v, i
 // on each of four SIMDs, so one output tile can reach half of the matrix rate and
 // two all of it; below that by staging, whose index arithmetic and latency are
 // kept small (one row of the halo per thread group, loads in batches, two or three
-// waves a SIMD).  Before and after, at 128^3: 16 -> 16 channels 78 -> 52 us, 48 -> 16 215
-// -> 121 us (0.29 of the BF16 peak), and at 64^3 96 -> 32 136 -> 45 us (0.39).
+// waves a SIMD).  Before and after, each layer repeated alone, at 128^3: 16 -> 16
+// channels 78 -> 52 us, 48 -> 16 215 -> 121 us (0.29 of the BF16 peak), and at 64^3
+// 96 -> 32 136 -> 45 us (0.39).  A trace of the whole network has a tenth more.
 constexpr int kTileX = 16, kTileZ = 4;
 constexpr int kHaloX = kTileX + 2, kHaloZ = kTileZ + 2;
 
@@ -300,7 +301,7 @@ void k_conv3(ConvArgs p) {
 // Bound by the LDS reads (196 bytes a lane per 27 instructions) close to the
 // matrix cores, and by staging between them.  Training step at 128^3: 5070 us in
 // all layers with every tap restaging its own transposed chunk (and 250 us for the
-// bias in a kernel of its own), 820 us now, 0.14 of the BF16 peak.
+// bias in a kernel of its own), 730 us now, 0.15 of the BF16 peak.
 struct WgradArgs {
   ConvIn in;
   const uint16_t* dy;   // BF16 [N][cout_pad]
