@@ -136,19 +136,19 @@ __global__ __launch_bounds__(kGradThreads) void k_sfe_grad(
     __syncthreads();
     if (wave == 0 && sub == 0 && atom < n_atoms) {
       double* o = out + ((size_t)blockIdx.x * n_atoms + atom) * 3;
-      const double pos[3] = {at[i].x, at[i].y, at[i].z};
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         double v = 0.0;
         for (int w = 0; w < kGradThreads / 64; ++w)
           for (int k = 0; k < subs; ++k) v += s_red[w][k * lanes + al][c];
-        o[c] = fabs(pos[c]) < kFarAway ? v * scale : __longlong_as_double(0x7ff8000000000000);
+        o[c] = v * scale;
       }
     }
   }
 }
 
-// out[i] = sum over the nb partial rows of part[b][i].  A workgroup takes
+// out[i] = sum over the nb partial rows of part[b][i] (part may be out), and NaN for
+// an infinite coordinate, whose pair force is 0 times infinity.  A workgroup takes
 // kGradRedCols columns; thread group r of kGradRedRows adds rows r, r + kGradRedRows, ...
 // in row order and the groups are added in order (fixed, so deterministic).
 // Bound by the latency of a thread's loads in turn: 126 us for 512 rows x 600
@@ -156,18 +156,19 @@ __global__ __launch_bounds__(kGradThreads) void k_sfe_grad(
 constexpr int kGradRedCols = 16, kGradRedRows = 16;
 
 __global__ __launch_bounds__(kGradRedCols* kGradRedRows) void k_sfe_grad_reduce(
-    const double* __restrict__ part, int nb, int n3, double* __restrict__ out) {
+    const double* part, int nb, int n3, const double4* __restrict__ atoms, double* out) {
   __shared__ double red[kGradRedRows][kGradRedCols];
   const int c = threadIdx.x % kGradRedCols, r = threadIdx.x / kGradRedCols;
   const int i = blockIdx.x * kGradRedCols + c;
   double v = 0.0;
   if (i < n3)
     for (int b = r; b < nb; b += kGradRedRows) v += part[(size_t)b * n3 + i];
+  const double pos = r == 0 && i < n3 ? reinterpret_cast<const double*>(atoms + i / 3)[i % 3] : 0.0;
   red[r][c] = v;
   __syncthreads();
   if (r == 0 && i < n3) {
     for (int k = 1; k < kGradRedRows; ++k) v += red[k][c];
-    out[i] = v;
+    out[i] = fabs(pos) < kFarAway ? v : __longlong_as_double(0x7ff8000000000000);
   }
 }
 

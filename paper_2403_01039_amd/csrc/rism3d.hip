@@ -1761,7 +1761,7 @@ rism3d_status rism3d_sfe_gradient(const rism3d_problem* pr, const rism3d_opts* o
   }
   // One partial row of 3 n_atoms doubles per workgroup column, kept in the
   // spectrum section (scratch between iterations).  About 2048 workgroups in
-  // all; a single column writes the result directly.
+  // all; a single column writes its row to the result, which the sum then passes over.
   const size_t tiles = (L.N + kGradTile - 1) / kGradTile;
   const size_t per = (size_t)grad_lanes(L.n_atoms) * grad_atoms_per_lane(L.n_atoms);
   const size_t chunks = (L.n_atoms + per - 1) / per;
@@ -1785,12 +1785,11 @@ rism3d_status rism3d_sfe_gradient(const rism3d_problem* pr, const rism3d_opts* o
     default: launch_sfe_grad_nv<8>(L, ws, g, pr->spacing, sc, scale, grid, dst, s); break;
   }
   LAUNCH_CHECK();
-  if (nb > 1) {
-    const int n3 = L.n_atoms * 3;
-    hipLaunchKernelGGL(k_sfe_grad_reduce, dim3(blocks_for(n3, kGradRedCols)),
-                       dim3(kGradRedCols * kGradRedRows), 0, s, dst, (int)nb, n3, grad);
-    LAUNCH_CHECK();
-  }
+  const int n3 = L.n_atoms * 3;
+  hipLaunchKernelGGL(k_sfe_grad_reduce, dim3(blocks_for(n3, kGradRedCols)),
+                     dim3(kGradRedCols * kGradRedRows), 0, s, dst, (int)nb, n3,
+                     at<double4>(ws, L.off_atoms), grad);
+  LAUNCH_CHECK();
   if (g_timer.on) {
     HIP_TRY(hipStreamSynchronize(s));
     g_timer.harvest();

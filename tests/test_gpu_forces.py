@@ -81,17 +81,18 @@ def test_atom_on_a_grid_point(R, O):
     assert np.abs(got - ref).max() <= 1e-10 * np.abs(ref).max()
 
 
-@pytest.mark.parametrize("n_atoms", [5, 70])
-def test_atom_out_of_range(R, n_atoms):
+@pytest.mark.parametrize("n_atoms,shape", [(5, (16, 18, 20)), (70, (16, 18, 20)), (70, (2, 6, 4))])
+def test_atom_out_of_range(R, n_atoms, shape):
     """A NaN coordinate makes that atom's gradient NaN; at an infinite coordinate
     the pair force is 0 times infinity along it; where the squared distance
-    overflows the gradient is 0.  The other atoms' gradients keep their bits."""
-    prob = inputs.small_problem(56, n_atoms=n_atoms, shape=(16, 18, 20), radius=5.0)
-    g = torch.tensor(inputs.synthetic_distribution(prob, 56, exclusion=1.0), device="cuda")
+    overflows the gradient is 0.  The other atoms' gradients keep their bits.  (The
+    last grid has one workgroup, whose sums pass over the result in place.)"""
+    prob = inputs.small_problem(56, n_atoms=n_atoms, shape=shape, radius=5.0)
+    g = torch.tensor(inputs.synthetic_distribution(prob, 56, exclusion=0.0), device="cuda")
     ref = _solver(R, prob)[0].sfe_gradient(g)
     for x in (np.nan, np.inf, -1e200):
         for axis in range(3):
-            p = inputs.small_problem(56, n_atoms=n_atoms, shape=(16, 18, 20), radius=5.0)
+            p = inputs.small_problem(56, n_atoms=n_atoms, shape=shape, radius=5.0)
             p.solute.xyz[2, axis] = x
             got = _solver(R, p)[0].sfe_gradient(g)
             others = [a for a in range(n_atoms) if a != 2]
