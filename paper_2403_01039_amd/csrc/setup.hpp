@@ -95,8 +95,8 @@ struct ExpNeg {
 // evaluated where no point of the wave is nearer).  128^3, 200 atoms, 5 sites: 1439 us
 // with a square root, two divisions and the library's exp at one point a thread, 642
 // us now (45 FP64 operations a pair, 0.75 of the FP64 issue rate), both repeated back
-// to back.  Behind the kernels that write the atoms a trace has 1446 and 760 us: the
-// scalar loads then wait for memory (0.63 of the issue rate).
+// to back.  Behind the kernels that write the atoms traces have 1446 and 700 to 760 us:
+// the scalar loads then wait for memory.
 //
 // A small grid has too few waves to hide the scalar loads, whose data, just
 // written, is in no nearby cache: it waits for memory atom after atom.  STAGE
